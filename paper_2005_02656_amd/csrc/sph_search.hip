@@ -950,11 +950,16 @@ again:
         const float M = sqrtf(half2) + R + sqrtf(diag2);
         const float e2 = M * M * 0x1p-18f;
         const bool product = __builtin_amdgcn_readfirstlane(!wide && e2 < 0x1p-10f * r2min) != 0;
-        // this lane's share of the targets' matrix, and the accumulators' starts
+        // this lane's share of the targets' matrix, and the accumulators' starts (a
+        // target at no position is infinitely far, one without a reach has none:
+        // the products hold no NaN, whose sign bit would accept)
         const float ax = fa.x - ctr[0], ay = fa.y - ctr[1], az = fa.z - ctr[2];
-        const float a2 = ax * ax + ay * ay + az * az;
-        const float bmat = s == 0 ? -2.0f * ax : s == 1 ? -2.0f * ay : s == 2 ? -2.0f * az : 1.0f;
-        const float accA = a2 - (fa.r2 + e2);
+        const float r2a = ax * ax + ay * ay + az * az;
+        const bool placed = r2a < INFINITY;
+        const float a2 = placed ? r2a : INFINITY;
+        const float comp = s == 0 ? -2.0f * ax : s == 1 ? -2.0f * ay : -2.0f * az;
+        const float bmat = s == 3 ? 1.0f : placed ? comp : 0.0f;
+        const float accA = fa.r2 < INFINITY ? a2 - (fa.r2 + e2) : INFINITY;
 
         // tests the open window's first nv entries against the targets
         auto test = [&](int nv) {
@@ -967,7 +972,8 @@ again:
                 const bool ok = u < nv;
                 const int32_t id = ok ? (int32_t)S.queue[qbase + u] : 0;
                 const Pos4f q = pf[id];
-                float x = q.x, y = q.y, z = q.z, w = q.r2, w2 = ok ? 1.0f : 0.0f;
+                float x = q.x, y = q.y, z = q.z, w2 = ok ? 1.0f : 0.0f;
+                float w = q.r2 >= 0.0f ? q.r2 : 0.0f;   // (no number: no reach)
                 if (product) {
                     x -= ctr[0];
                     y -= ctr[1];
@@ -975,9 +981,16 @@ again:
                     if (kPer & 1) x = fmaf(-P.wrapL[0], rintf(x * P.wrapInvL[0]), x);
                     if (kPer & 2) y = fmaf(-P.wrapL[1], rintf(y * P.wrapInvL[1]), y);
                     if (kPer & 4) z = fmaf(-P.wrapL[2], rintf(z * P.wrapInvL[2]), z);
-                    // (past the end: a distance that nothing reaches)
-                    w2 = ok ? fmaf(z, z, fmaf(y, y, x * x)) : 1e30f;
-                    w = w2 - (w + e2);
+                    // past the end, and at no position: an infinite distance,
+                    // which no reach of any size accepts (an accepted place past
+                    // the end would name whatever the queue holds there)
+                    w2 = fmaf(z, z, fmaf(y, y, x * x));
+                    const bool there = ok && w2 < INFINITY;
+                    x = there ? x : 0.0f;
+                    y = there ? y : 0.0f;
+                    z = there ? z : 0.0f;
+                    w = there && w < INFINITY ? w2 - (w + e2) : INFINITY;
+                    w2 = there ? w2 : INFINITY;
                 }
                 const int at = (p >> 5) * kWalkRow + (p & 31);
                 S.rec[0][at] = x;
@@ -1010,7 +1023,7 @@ again:
                             m, __float_as_uint(dA[r]) | __float_as_uint(dB[r]), 31);
                 }
             } else {
-                const uint32_t far2 = __float_as_uint(fa.r2);
+                const uint32_t far2 = __float_as_uint(fa.r2 >= 0.0f ? fa.r2 : 0.0f);
 #pragma unroll 2
                 for (int e = 0; e < 32; ++e) {
                     const int at = s * kWalkRow + e;
