@@ -65,7 +65,16 @@ __device__ void domain_record(const Params& P, Domain* d, const double (&r)[7], 
         d->scale[k] = (D[k] > 0.0) ? 2097152.0 / D[k] : 0.0;
         ext = fmax(ext, D[k]);
     }
-    d->walk_slack = (float)(ext * 0x1p-20);
+    // the walk's unit: ext is 1/2 .. 1 of it (1 where ext is 0 or no finite number)
+    int e = 0;
+    if (ext > 0.0 && ext < INFINITY) frexp(ext, &e);
+    const double sc = ldexp(1.0, -max(-1022, min(1022, e)));
+    d->walk_scale = sc;
+    d->walk_slack = (float)(ext * sc * 0x1p-20);
+    for (int k = 0; k < 3; ++k) {
+        d->wrap[k] = P.periodic[k] ? (float)(P.L[k] * sc) : 0.0f;
+        d->wrap_inv[k] = P.periodic[k] ? (float)(1.0 / (P.L[k] * sc)) : 0.0f;
+    }
     int level = 0;
     for (int l = P.lcap; l >= 0; --l) {
         bool ok = true;

@@ -46,7 +46,6 @@ struct Params {
     int precision;
     int cand_cap;          // candidate-list capacity of the fused step (0: off)
     double wrapLd[3], wrapInvLd[3];  // L and 1/L on periodic axes, 0 on open ones
-    float wrapL[3], wrapInvL[3];     // the same in FP32 (the fused step's candidate walk)
     // kernel tables (section 4.5): tab_n values of S_n and dS_n/dv at v_i = i dv,
     // dv = 2/(tab_n - 1), entry i holding the values at nodes i and i+1; 0 = off
     int tab_n;
@@ -75,9 +74,14 @@ struct Domain {
     uint32_t u_varies;         // some u differs from slot 0's (set by the cell build)
     uint32_t arrived;          // workgroups done (last_block); 0 between launches
     int32_t reach_level;       // fused step: level of the blocks that bound each walk's reach
-    float walk_slack;          // 2^-20 x the largest extent (FP32 candidate walk)
+    // FP32 candidate walk: its unit of length as a power of two (1/unit), and in
+    // that unit 2^-20 x the largest extent, and L and 1/L of the periodic axes
+    double walk_scale;
+    float walk_slack;
+    float wrap[3], wrap_inv[3];
     int64_t built_n;
 };
+static_assert(sizeof(Domain) <= 256, "the workspace's layout stands");
 
 // ---------------------------------------------------------------- packed records
 // Gathered per neighbour; one record is a few 16-byte loads instead of one
@@ -85,10 +89,13 @@ struct Domain {
 struct alignas(32) Pos4 {
     double x, y, z, h;
 };
-// the candidate walk's record (fused step): FP32 offsets of the position from
-// the key domain's low corner and the particle's squared short reach, widened
-// to cover the rounding of the FP32 test ((2 lambda h + slack)^2 (1 + 2^-18),
-// h rounded up), so the walk's candidates are a superset of the exact ones
+// the candidate walk's record: FP32 offsets of the position from the key
+// domain's low corner and the particle's squared short reach, widened to cover
+// the rounding of the FP32 test ((2 lambda h + slack)^2 (1 + 2^-18), h rounded
+// up), so the walk's candidates are a superset of the exact ones.  Lengths are
+// in units of a power of two near the domain's largest extent: whatever the
+// caller's units, squares stay far inside FP32's range (in units of the caller,
+// an h beyond 1e19 or below 1e-19 found nothing), and the shift rounds nothing.
 struct alignas(16) Pos4f {
     float x, y, z, r2;
 };
@@ -236,11 +243,13 @@ SPH_DEV float up_f32(double v)
 }
 
 // the walk record of a particle for the reach 2 kap h, k2s an FP32 bound of 2 kap
+// (an h that is no number reaches nothing)
 SPH_DEV Pos4f walk_record(const Domain* dom, const Pos4& q, float k2s)
 {
-    const float R = fmaf(k2s, up_f32(q.h), dom->walk_slack);
-    return Pos4f{(float)(q.x - dom->lo[0]), (float)(q.y - dom->lo[1]), (float)(q.z - dom->lo[2]),
-                 (R * R) * kWalkGrow};
+    const double s = dom->walk_scale;
+    const float R = q.h == q.h ? fmaf(k2s, up_f32(q.h * s), dom->walk_slack) : 0.0f;
+    return Pos4f{(float)((q.x - dom->lo[0]) * s), (float)((q.y - dom->lo[1]) * s),
+                 (float)((q.z - dom->lo[2]) * s), (R * R) * kWalkGrow};
 }
 
 // The level of the blocks that bound the group walk's reach: the finest one at

@@ -464,7 +464,7 @@ __global__ __launch_bounds__(kBlock) void k_find_neighbors(Params P, Domain* __r
 // It may fuse multiply-adds: the widening factor of the reach covers its FP32
 // rounding either way
 template <int kPer>
-__device__ __forceinline__ float walk_r2(const Params& P, float xa, float ya, float za, float xb,
+__device__ __forceinline__ float walk_r2(const Domain& D, float xa, float ya, float za, float xb,
                                          float yb, float zb)
 {
 #pragma clang fp contract(fast)
@@ -472,7 +472,7 @@ __device__ __forceinline__ float walk_r2(const Params& P, float xa, float ya, fl
     float d[3] = {xb - xa, yb - ya, zb - za};
 #pragma unroll
     for (int c = 0; c < 3; ++c)
-        if (kPer & (1 << c)) d[c] = fmaf(-P.wrapL[c], rintf(d[c] * P.wrapInvL[c]), d[c]);
+        if (kPer & (1 << c)) d[c] = fmaf(-D.wrap[c], rintf(d[c] * D.wrap_inv[c]), d[c]);
     return d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
 }
 
@@ -562,7 +562,7 @@ __device__ __forceinline__ void refit_target(
                 for (int u = 0; u < 4; ++u) r[u] = pf[b + u];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const float r2 = walk_r2<kPer>(P, fa.x, fa.y, fa.z, r[u].x, r[u].y, r[u].z);
+                    const float r2 = walk_r2<kPer>(D, fa.x, fa.y, fa.z, r[u].x, r[u].y, r[u].z);
                     if (b + u < e && b + u != (int32_t)a &&
                         __float_as_uint(r2) < max(far2, __float_as_uint(r[u].r2 * sc)))
                         take(b + u);
@@ -686,7 +686,7 @@ __global__ __launch_bounds__(kBlock) SPH_WAVES_EXACT(5) void k_candidates_full(
                 // All three are non-negative floats, whose order is that of their
                 // bit patterns as unsigned integers: one integer max and one
                 // compare (a float max quiets NaNs first, one more instruction).
-                const float r2 = walk_r2<kPer>(P, fa.x, fa.y, fa.z, q.x, q.y, q.z);
+                const float r2 = walk_r2<kPer>(D, fa.x, fa.y, fa.z, q.x, q.y, q.z);
                 const bool near = __float_as_uint(r2) < max(far2, __float_as_uint(q.r2 * sc));
                 if (near & (b != self)) {
                     // a neighbour of a grown h redoes its own walk at full reach
@@ -836,16 +836,20 @@ __global__ __launch_bounds__(64 * kSplit) SPH_WAVES_EXACT(kSplit > 1 ? 3 : SPH_W
     const int64_t a = live ? a0 + j : P.n - 1;
     const int cap = P.cand_cap;
     const int nax = dom->ncell_axis, level = dom->level;
+    // (every FP32 length here is in the walk's unit)
     const float slack = dom->walk_slack;
-    float ce[3], inv[3];
+    const double unit = dom->walk_scale;
+    float ce[3], inv[3], wl[3], wi[3];
 #pragma unroll
     for (int x = 0; x < 3; ++x) {
-        ce[x] = (float)dom->cell[x];
+        ce[x] = (float)(dom->cell[x] * unit);
         inv[x] = ce[x] > 0.0f ? 1.0f / ce[x] : 0.0f;
+        wl[x] = dom->wrap[x];
+        wi[x] = dom->wrap_inv[x];
     }
     const Pos4f fa = pf[a];
     const float k2 = up_f32(2.0 * kap);
-    const float ha = up_f32(p4[a].h);
+    const float ha = up_f32(p4[a].h * unit);
     // targets of one block of 4 x 4 x 4 cells are walked together
     const int glevel = level > 2 ? level - 2 : 0, rlevel = dom->reach_level;
     const uint32_t block = (uint32_t)(keys[a] >> (3 * (kKeyBits - glevel)));
@@ -901,8 +905,9 @@ again:
         const float r2min = uniform(row_min(member ? fa.r2 : INFINITY));
         // the largest h that the targets' candidates can have: of the group's
         // block at the reach level (no finer than the group's) and its neighbours
-        float hb = lane < 27 ? up_f32(reach_neighbor(P, rlevel, mine >> (3 * (glevel - rlevel)),
-                                                     lane, reach))
+        float hb = lane < 27 ? up_f32(unit * reach_neighbor(
+                                                 P, rlevel, mine >> (3 * (glevel - rlevel)), lane,
+                                                 reach))
                              : 0.0f;
         hb = row_max(hb);
         hb = fmaxf(uniform(hb), __builtin_bit_cast(float, __builtin_amdgcn_readlane(
@@ -939,7 +944,7 @@ again:
                 b1 = min(b1, 2 * nax - 1);
                 // the nearest image to the centre is the nearest to every
                 // target when no pair in reach spans half the box
-                wide = wide || !(half + R < 0.49f * P.wrapL[x]);
+                wide = wide || !(half + R < 0.49f * wl[x]);
             } else {
                 b0 = min(max(b0, 0), nax - 1);
                 b1 = min(max(b1, 0), nax - 1);
@@ -951,15 +956,15 @@ again:
         const float e2 = M * M * 0x1p-18f;
         const bool product = __builtin_amdgcn_readfirstlane(!wide && e2 < 0x1p-10f * r2min) != 0;
         // this lane's share of the targets' matrix, and the accumulators' starts (a
-        // target at no position is infinitely far, one without a reach has none:
-        // the products hold no NaN, whose sign bit would accept)
+        // target at no position is infinitely far: the products hold no NaN, whose
+        // sign bit would accept)
         const float ax = fa.x - ctr[0], ay = fa.y - ctr[1], az = fa.z - ctr[2];
         const float r2a = ax * ax + ay * ay + az * az;
         const bool placed = r2a < INFINITY;
         const float a2 = placed ? r2a : INFINITY;
         const float comp = s == 0 ? -2.0f * ax : s == 1 ? -2.0f * ay : -2.0f * az;
         const float bmat = s == 3 ? 1.0f : placed ? comp : 0.0f;
-        const float accA = fa.r2 < INFINITY ? a2 - (fa.r2 + e2) : INFINITY;
+        const float accA = a2 - (fa.r2 + e2);
 
         // tests the open window's first nv entries against the targets
         auto test = [&](int nv) {
@@ -972,15 +977,14 @@ again:
                 const bool ok = u < nv;
                 const int32_t id = ok ? (int32_t)S.queue[qbase + u] : 0;
                 const Pos4f q = pf[id];
-                float x = q.x, y = q.y, z = q.z, w2 = ok ? 1.0f : 0.0f;
-                float w = q.r2 >= 0.0f ? q.r2 : 0.0f;   // (no number: no reach)
+                float x = q.x, y = q.y, z = q.z, w = q.r2, w2 = ok ? 1.0f : 0.0f;
                 if (product) {
                     x -= ctr[0];
                     y -= ctr[1];
                     z -= ctr[2];
-                    if (kPer & 1) x = fmaf(-P.wrapL[0], rintf(x * P.wrapInvL[0]), x);
-                    if (kPer & 2) y = fmaf(-P.wrapL[1], rintf(y * P.wrapInvL[1]), y);
-                    if (kPer & 4) z = fmaf(-P.wrapL[2], rintf(z * P.wrapInvL[2]), z);
+                    if (kPer & 1) x = fmaf(-wl[0], rintf(x * wi[0]), x);
+                    if (kPer & 2) y = fmaf(-wl[1], rintf(y * wi[1]), y);
+                    if (kPer & 4) z = fmaf(-wl[2], rintf(z * wi[2]), z);
                     // past the end, and at no position: an infinite distance,
                     // which no reach of any size accepts (an accepted place past
                     // the end would name whatever the queue holds there)
@@ -989,7 +993,7 @@ again:
                     x = there ? x : 0.0f;
                     y = there ? y : 0.0f;
                     z = there ? z : 0.0f;
-                    w = there && w < INFINITY ? w2 - (w + e2) : INFINITY;
+                    w = there ? w2 - (w + e2) : INFINITY;
                     w2 = there ? w2 : INFINITY;
                 }
                 const int at = (p >> 5) * kWalkRow + (p & 31);
@@ -1023,11 +1027,11 @@ again:
                             m, __float_as_uint(dA[r]) | __float_as_uint(dB[r]), 31);
                 }
             } else {
-                const uint32_t far2 = __float_as_uint(fa.r2 >= 0.0f ? fa.r2 : 0.0f);
+                const uint32_t far2 = __float_as_uint(fa.r2);
 #pragma unroll 2
                 for (int e = 0; e < 32; ++e) {
                     const int at = s * kWalkRow + e;
-                    const float r2 = walk_r2<kPer>(P, fa.x, fa.y, fa.z, S.rec[0][at],
+                    const float r2 = walk_r2<kPer>(*dom, fa.x, fa.y, fa.z, S.rec[0][at],
                                                    S.rec[1][at], S.rec[2][at]);
                     const bool near =
                         __float_as_uint(r2) < max(far2, __float_as_uint(S.rec[3][at])) &&
@@ -1130,7 +1134,7 @@ again:
         load_cell(qb, next, next_g2);
         for (int q0 = qb; q0 < qe; q0 += 64) {
             const CellRange cr = next;
-            const float Rc = fmaf(k2, fmaxf(hm, up_f32(cr.hmax)), slack);
+            const float Rc = fmaf(k2, fmaxf(hm, up_f32(cr.hmax * unit)), slack);
             const int cnt = next_g2 < Rc * Rc ? cr.e - cr.s : 0;
             if (q0 + 64 < qe) load_cell(q0 + 64, next, next_g2);   // meanwhile
             // places in the queue: an inclusive scan over the lanes

@@ -49,7 +49,7 @@ def _step(w, **kw):
 
 
 @pytest.mark.parametrize("n,periodic", [(3001, (1, 1, 1)), (3001, (0, 1, 0)), (26001, (0, 0, 0))])
-@pytest.mark.parametrize("e", [56])
+@pytest.mark.parametrize("e", [-80, -64, 56, 64, 80])
 def test_step_in_other_units(n, periodic, e):
     w = _random(n, periodic)
     f0, p0, st0 = _step(w)
@@ -98,3 +98,28 @@ def test_particles_without_a_position_or_a_reach(n, sign, field):
         mine = P[P[:, 0] == i]
         assert nc[i] == gather.sum() and ns[i] == both.sum(), i
         assert np.array_equal(mine[:, 1], np.nonzero(both)[0]), i
+
+
+@pytest.mark.parametrize("n,periodic", [(3001, (1, 0, 1)), (70001, (0, 0, 0))])
+@pytest.mark.parametrize("e", [-80, 80])
+def test_stage_calls_in_other_units(n, periodic, e):
+    """update_h and the neighbour lists by the stage calls, and a step with a clamp
+    above the fused step's, which uses them."""
+    w = _random(n, periodic)
+    got = []
+    for u in (w, _scaled(w, e)):
+        cfg, _ = configs(u, ng_max=600, n_target=60.0, newton_iters=2)
+        r = Run(u, cfg)
+        sph.build_cells(cfg, r.parts, r.ws)
+        sph.update_h(cfg, r.parts, r.ws)
+        h = r.by_id("h")
+        sph.find_neighbors(cfg, r.parts, r.ws)
+        assert r.status() == (0, 0)
+        got.append((h, r.neighbor_pairs(), _step(u, h_ratio_max=2.0)))
+    (h0, p0, s0), (h1, p1, s1) = got
+    assert np.array_equal(h1, h0 * 2.0 ** e)
+    assert all(np.array_equal(a, b) for a, b in zip(p0, p1))
+    assert s0[2] == s1[2]   # (an open corner may leave a tau singular, in either unit)
+    for k, p in POWERS.items():
+        assert np.array_equal(s1[0][k], s0[0][k] * 2.0 ** (p * e)), k
+    assert all(np.array_equal(a, b) for a, b in zip(s0[1], s1[1]))
