@@ -21,6 +21,7 @@
 #include <cmath>
 
 #include "sph_common.h"
+#include "sph_walk_cell.h"
 
 namespace sph {
 namespace {
@@ -1098,15 +1099,11 @@ again:
         // (of them this wavefront's: qb .. qe - 1)
         const int qb = parts > 1 ? ncells * wv / kSplit : 0;
         const int qe = parts > 1 ? ncells * (wv + 1) / kSplit : ncells;
-        const int nyz = nc[1] * nc[2];
-        const float ryz1 = 1.0f / (float)nyz, rz1 = 1.0f / (float)nc[2];
+        const float ryz1 = 1.0f / (float)(nc[1] * nc[2]), rz1 = 1.0f / (float)nc[2];
         auto load_cell = [&](int q0, CellRange& cr, float& g2) {
             const int q = q0 + lane;
-            // (quotients by reciprocals: exact below 2^20, and clamped in any case)
-            const int ix = min((int)(((float)q + 0.5f) * ryz1), nc[0] - 1);
-            const int ryz = q - ix * nyz;
-            const int iy = min((int)(((float)ryz + 0.5f) * rz1), nc[1] - 1);
-            const int iz = min(max(ryz - iy * nc[2], 0), nc[2] - 1);
+            int ix, iy, iz;
+            box_cell(q, nc[0], nc[1], nc[2], ryz1, rz1, ix, iy, iz);
             const int at[3] = {c0[0] + ix, c0[1] + iy, c0[2] + iz};
             uint32_t code = 0u;
             g2 = 0.0f;
