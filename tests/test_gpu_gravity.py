@@ -114,3 +114,22 @@ def test_gravity_rejects_periodic_axes_and_bad_parameters():
             sph.gravity(c, parts, ws, gws, bad.get("G", 1.0), bad.get("eps", 0.0),
                         bad.get("theta", 0.5))
         assert e.value.status == 1
+
+
+def test_gravity_of_particles_whose_squared_distance_overflows():
+    """Clusters 1e160 apart: their pull on each other is below every number, so
+    the sums are those of the clusters alone."""
+    rng = np.random.default_rng(2)
+    n = 24
+    X = rng.normal(size=(n, 3))
+    X[n // 2:] += np.array([1e160, 0.0, 0.0])      # (one point there: no unit is left)
+    X[n // 2:] = X[n // 2] + np.arange(n - n // 2)[:, None] * np.array([0.0, 1.0, 0.0])
+    a = dict(x=X[:, 0].copy(), y=X[:, 1].copy(), z=X[:, 2].copy(), vx=np.zeros(n),
+             vy=np.zeros(n), vz=np.zeros(n), m=rng.uniform(0.5, 1.5, n), u=np.ones(n),
+             h=np.full(n, 0.05), id=np.arange(n, dtype=np.int64))
+    w = inputs.Workload("far", a, inputs.base_params(periodic=(0, 0, 0)))
+    g, _ = _gpu_gravity(w, 0.0)
+    for part in (slice(0, n // 2), slice(n // 2, n)):
+        d = oracle.gravity_direct(a["x"][part], a["y"][part], a["z"][part], a["m"][part], G, EPS)
+        for k in range(3):
+            assert np.max(np.abs(g[k][part] - d[k]) / d[3]) < TOL
