@@ -21,11 +21,14 @@ namespace {
 constexpr int kGravStack = 7 * kMaxLevel + 1;   // deepest depth-first stack
 
 // Particle numbers up to which 16 and 4 wavefronts share a set of 64 targets.
-// Cell build, tree and walk of an Evrard sphere with 16, 4 and 1: 10,000
-// particles 251, 326, 802 us; 30,000 420, 503, 1008; 100,000 1377, 963, 1420;
-// 250,000 3288, 2038, 2133; 500,000 10174, 4288, 3266.
+// Cell build, tree and walk of an Evrard sphere with 16, 4 and 1 at theta = 0.5:
+// 10,000 particles 251, 326, 802 us; 30,000 420, 503, 1008; 100,000 1377, 963, 1420.
+// The walk alone with 4 and 1, Evrard | even: 160,000 particles 1281, 1564 | 1109,
+// 1395 us; 200,000 1573, 1882 | 1281, 1519 (at theta = 1 632, 656 | 532, 463);
+// 262,144, where the tree gains a level, 2714, 2488 | 2832, 2547 (1028, 768 | 1067,
+// 759); 330,000 3121, 2599 | 3290, 2641.
 constexpr int64_t kSplit16 = 40960;
-constexpr int64_t kSplit4 = 262144;
+constexpr int64_t kSplit4 = 200000;
 
 // 1/r from r^2.  kFar (squares may overflow): those beyond the largest number
 // count as it and their terms come out zero, as with 1/sqrt, where the iteration

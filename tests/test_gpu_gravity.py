@@ -133,3 +133,14 @@ def test_gravity_of_particles_whose_squared_distance_overflows():
         d = oracle.gravity_direct(a["x"][part], a["y"][part], a["z"][part], a["m"][part], G, EPS)
         for k in range(3):
             assert np.max(np.abs(g[k][part] - d[k]) / d[3]) < TOL
+
+
+@pytest.mark.parametrize("n", [40960, 40961, 200000, 200001])
+def test_gravity_on_both_sides_of_the_shared_walks(n):
+    """16, 4 and 1 wavefronts to a set of targets, at the particle numbers where
+    their number changes: 64 random targets against the oracle's walk."""
+    w = _gaussian(n, seed=n)
+    g, ocfg = _gpu_gravity(w, 0.5)
+    tgt = np.random.default_rng(n).choice(n, 64, replace=False)
+    o = _oracle_tree(w, ocfg, 0.5, targets=tgt)
+    assert max(np.max(np.abs(g[k][tgt] - o[k][tgt]) / o[3][tgt]) for k in range(3)) < TOL
