@@ -26,10 +26,36 @@ __device__ __forceinline__ double block_sum(double v, double* lds)
     return s;
 }
 
-// The whole end of a step in one launch (three before: the time step, this, the
-// sums): every workgroup forms the time step for itself (kStep) and the last one
-// to finish adds up the partial sums, in a fixed order.  16 + 10 + 5 us and two
-// gaps -> 33 us at 262,144 particles, 6 + 6 + 2 -> 12 at 1,000.
+// the partial sums of `blocks` workgroups, added in a fixed order, into the globals
+template <class Get>
+__device__ __forceinline__ void finish_sums(int blocks, double dt, sph_globals* g, double* lds,
+                                            Get&& get)
+{
+    double out[kNSum];
+    for (int k = 0; k < kNSum; ++k) {
+        double v = 0.0;
+        for (int b = threadIdx.x; b < blocks; b += kBlock) v += get(b * 10 + k);
+        out[k] = block_sum(v, lds);
+    }
+    if (threadIdx.x == 0) {
+        g->mass = out[0];
+        g->mom[0] = out[1]; g->mom[1] = out[2]; g->mom[2] = out[3];
+        g->ang[0] = out[4]; g->ang[1] = out[5]; g->ang[2] = out[6];
+        g->e_kin = out[7];
+        g->e_int = out[8];
+        g->t = g->t + dt;
+        g->dt = dt;
+        g->dt_m1 = dt;
+    }
+}
+
+// kStep: the whole end of a step in one launch (three before: the time step, this,
+// the sums): every workgroup forms the time step for itself and the last one to
+// finish adds up the partial sums.  16 + 10 + 5 us and two gaps -> 33 us at 262,144
+// particles, 6 + 6 + 2 -> 12 at 1,000.  sph_integrate by itself has no launch to
+// save but the sums', and the workgroups' arrivals on one counter cost more than
+// that: its sums are a launch of their own (the call at 262,144: 44 us in one
+// launch, 37 in two).
 template <bool kStep>
 __global__ __launch_bounds__(kBlock) void k_integrate(Params P, Domain* __restrict__ dom,
                                                       sph_globals* g, IntState S,
@@ -79,25 +105,22 @@ __global__ __launch_bounds__(kBlock) void k_integrate(Params P, Domain* __restri
     __shared__ double lds[kBlock / 64];
     for (int k = 0; k < kNSum; ++k) {
         double s = block_sum(acc[k], lds);
-        if (threadIdx.x == 0) put_partial(&part[blockIdx.x * 10 + k], s);
+        if (threadIdx.x == 0) {
+            if constexpr (kStep) put_partial(&part[blockIdx.x * 10 + k], s);
+            else part[blockIdx.x * 10 + k] = s;
+        }
     }
-    if (!last_block(&dom->arrived, gridDim.x)) return;
-    double out[kNSum];
-    for (int k = 0; k < kNSum; ++k) {
-        double v = 0.0;
-        for (int b = threadIdx.x; b < (int)gridDim.x; b += kBlock) v += get_partial(&part[b * 10 + k]);
-        out[k] = block_sum(v, lds);
+    if constexpr (kStep) {
+        if (last_block(&dom->arrived, gridDim.x))
+            finish_sums((int)gridDim.x, dt, g, lds, [&](int i) { return get_partial(&part[i]); });
     }
-    if (threadIdx.x == 0) {
-        g->mass = out[0];
-        g->mom[0] = out[1]; g->mom[1] = out[2]; g->mom[2] = out[3];
-        g->ang[0] = out[4]; g->ang[1] = out[5]; g->ang[2] = out[6];
-        g->e_kin = out[7];
-        g->e_int = out[8];
-        g->t = g->t + dt;
-        g->dt = dt;
-        g->dt_m1 = dt;
-    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_sums_finish(const double* __restrict__ part, int blocks,
+                                                        sph_globals* g)
+{
+    __shared__ double lds[kBlock / 64];
+    finish_sums(blocks, g->dt, g, lds, [&](int i) { return part[i]; });
 }
 
 }  // namespace
@@ -109,8 +132,12 @@ hipError_t launch_integrate(const Params& P, const Ws& W, sph_particles* p, sph_
                p->m, p->ax, p->ay, p->az, p->du};
     int64_t nb = (P.n + kBlock - 1) / kBlock;
     int grid = nb < kSumBlocks ? (int)nb : kSumBlocks;
-    if (step) k_integrate<true><<<grid, kBlock, 0, s>>>(P, W.dom, g, S, W.sums);
-    else k_integrate<false><<<grid, kBlock, 0, s>>>(P, W.dom, g, S, W.sums);
+    if (step) {
+        k_integrate<true><<<grid, kBlock, 0, s>>>(P, W.dom, g, S, W.sums);
+    } else {
+        k_integrate<false><<<grid, kBlock, 0, s>>>(P, W.dom, g, S, W.sums);
+        k_sums_finish<<<1, kBlock, 0, s>>>(W.sums, grid, g);
+    }
     return hipGetLastError();
 }
 
