@@ -505,7 +505,8 @@ __device__ __forceinline__ float walk_r2(const Domain& D, float xa, float ya, fl
 // targets grown: 30,011 random particles 296 -> 79 us; the 8 M blob 314 -> 245.  A
 // wavefront per target costs several times a lane's share of the machine, so it
 // is for 512 slots with few flagged ones (refit_few), a lane each for the others
-// (all of a 1 M lattice grown: 0.65 ms before, 0.77 now; 30,011: 0.14 both).
+// (a whole step with all particles grown, by lanes over an unbounded grid and now:
+// lattices of 262,144 1.62, 1.49 ms, 1 M 6.04, 5.77; 262,144 random 3.20, 2.61).
 // Both walk a target's cells, and write its candidates, in the same order.
 //
 // kMode 1: the targets whose h left the short reach (flag 2), marking every
@@ -617,7 +618,8 @@ __global__ __launch_bounds__(kBlock) SPH_WAVES_EXACT(5) void k_candidates_full(
 {
     if (dom->refit == 0u) return;
     // a bounded grid: a launch that finds nothing to do costs its workgroups'
-    // start (31,250 of them at 8 M particles: 110-190 us)
+    // start (31,250 of them at 8 M particles: 110-190 us); an XCD's workgroups
+    // take neighbouring slots, which share its L2
     constexpr uint32_t kWant = kMode == 1 ? 2u : 1u;
     const int64_t nt = (P.n + 511) / 512;
     const int share = refit_share(P);
@@ -625,9 +627,10 @@ __global__ __launch_bounds__(kBlock) SPH_WAVES_EXACT(5) void k_candidates_full(
     // candidates are staged in LDS, column per lane, and written out in
     // whole chunks of 8 (two 16-byte stores per lane)
     __shared__ int32_t stage[8][kBlock];
-    const int64_t w0 = (int64_t)blockIdx.x * (kBlock / 64) +
+    const int64_t waves = (int64_t)gridDim.x * (kBlock / 64);
+    const int64_t w0 = xcd_block(gridDim.x) * (kBlock / 64) +
                        __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    for (int64_t it = w0; it < nt * share; it += (int64_t)gridDim.x * (kBlock / 64)) {
+    for (int64_t it = w0; it < nt * share; it += waves) {
         const int64_t s0 = it / share * 512;
         const int g = (int)(it % share);
         // this lane's 8 of the 512 flags (the array has room for whole words)
@@ -658,7 +661,8 @@ __global__ __launch_bounds__(kBlock) SPH_WAVES_EXACT(5) void k_candidates_full(
             continue;
         }
         // a lane each: 8 of the wavefronts take 64 slots, others from round to round
-        const int64_t turn = it / share + (it / share >> 7);
+        // (a round advances a wavefront by waves / share sets of 512)
+        const int64_t per = waves / share, turn = it / share % per + it / share / per;
         if (share != 8 && ((g ^ (int)turn) & 7) != 0) continue;
         const int64_t a = s0 + 64 * (share != 8 ? g >> 3 : g) + lane;
         if (a >= P.n || flag[a] != kWant) continue;
@@ -1202,7 +1206,13 @@ again:
     }
 }
 
-constexpr int64_t kRefitGrid = 2048;   // workgroups of the refit launches
+// workgroups of the refit walks, as many as are resident at once (with 2,048 a part
+// waited for the others to end: 262,144 lattice particles grown, a step of 1.37 ms
+// took 1.59 in mixed precision); a multiple of 16, so that a wavefront's share of
+// 512 slots stays the same from round to round
+constexpr int64_t kRefitGrid = 1280;
+// and of the Newton pass after them
+constexpr int64_t kRefitNewtonGrid = 2048;
 
 // the candidate pass for the periodic axes of P: mode 0 short reach, 1 and 2
 // the full-reach refits
@@ -1211,7 +1221,7 @@ static void launch_candidates(int mode, const Params& P, const Ws& W, double kap
 {
     const int64_t waves = (P.n + 511) / 512 * refit_share(P);
     const int64_t blocks = (waves * 64 + kBlock - 1) / kBlock;
-    const int few = (int)(blocks < kRefitGrid ? blocks : kRefitGrid);
+    const int few = (int)(blocks < kRefitGrid ? (blocks + 15) / 16 * 16 : kRefitGrid);
     // the records hold the squared short reach; the full pass scales it by
     // at least (kap / lambda)^2 (the slack scales with it, which only widens)
     const double lam = fmin(kFusedReach, P.kappa);
@@ -1471,7 +1481,9 @@ __global__ __launch_bounds__(kBlock) SPH_WAVES_EXACT(kG == 1 ? 4 : 3) void k_upd
     if (dom->refit != 0u && lam > kFusedReach) {
         constexpr int kTargets = kBlock / kG;
         const int64_t nb = (P.n + kTargets - 1) / kTargets;
-        for (int64_t lb = blockIdx.x; lb < nb; lb += gridDim.x) {
+        for (int64_t bid = blockIdx.x; bid < grid_xcd(nb); bid += gridDim.x) {
+            const int64_t lb = xcd_block(nb, bid);
+            if (lb < 0) continue;
             const int64_t a = lb * kTargets + (int)threadIdx.x / kG;
             update_h_list<kPer, kTab, kG>(P, dom, nk, cand, p4, h, lam, flag, kNewtonRefit, lb);
             if (a < P.n && (int)threadIdx.x % kG == 0) p4[a].h = h[a];
@@ -1774,7 +1786,7 @@ hipError_t launch_fused_step(const Params& P, const Layout& L, const Ws& W, sph_
             launch_candidates(2, P, W, P.kappa, s);
         }
         const int64_t nb = (P.n + kBlock - 1) / kBlock;
-        const int grid = (int)(nb < kRefitGrid ? nb : kRefitGrid);
+        const int grid = (int)(nb < kRefitNewtonGrid ? nb : kRefitNewtonGrid);
         with_periodic(P, [&](auto per) {
             with_table(P, [&](auto tab) {
                 constexpr int kPer = decltype(per)::value;
