@@ -73,7 +73,11 @@ struct Domain {
     uint32_t mass_varies;      // some m differs from slot 0's (set by the cell build)
     uint32_t u_varies;         // some u differs from slot 0's (set by the cell build)
     uint32_t arrived;          // workgroups done (last_block); 0 between launches
-    int32_t reach_level;       // fused step: level of the blocks that bound each walk's reach
+    int32_t reach_level;       // level of the blocks that bound each group walk's reach
+    // stage calls: sampled targets whose h grows past, or whose candidates overrun,
+    // the reach at hand, and the reach (0: every target walks the cells by itself)
+    uint32_t stage_grown, stage_crowded;
+    double stage_reach;
     // FP32 candidate walk: its unit of length as a power of two (1/unit), and in
     // that unit 2^-20 x the largest extent, and L and 1/L of the periodic axes
     double walk_scale;

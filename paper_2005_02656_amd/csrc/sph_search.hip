@@ -207,19 +207,21 @@ __device__ __forceinline__ void check_cell_range(const Params& P, Domain* dom, d
 }
 
 // ---------------------------------------------------------------- cell-walk forms
-// (flag: only the targets it marks with 2, if any is marked)
+// (flag: only the targets it marks with 2, if any is marked, unless the stage call
+// has no reach and leaves all to this walk)
 __global__ __launch_bounds__(kBlock) void k_update_h(Params P, const Domain* __restrict__ dom,
                                                      const CellRange* __restrict__ cells,
                                                      const Pos4* __restrict__ p4,
                                                      double* __restrict__ h,
                                                      const uint8_t* __restrict__ flag)
 {
-    if (flag && dom->refit == 0u) return;
+    const bool some = flag && dom->stage_reach > 0.0;
+    if (some && dom->refit == 0u) return;
     const int64_t nb = (P.n + kBlock - 1) / kBlock;
     const int64_t lb = xcd_block(nb);
     if (lb < 0) return;
     const int64_t a = lb * kBlock + threadIdx.x;
-    if (a >= P.n || (flag && flag[a] != 2)) return;
+    if (a >= P.n || (some && flag[a] != 2)) return;
     const Domain D = *dom;
     const Pos4 pa = p4[a];
     const double xa = pa.x, ya = pa.y, za = pa.z;
@@ -249,18 +251,175 @@ __global__ __launch_bounds__(kBlock) void k_update_h(Params P, const Domain* __r
 
 __global__ void k_hmax_begin(Domain* d) { d->hmax_new_bits = ord_bits(0.0); }
 
+// The reach of sph_update_h's group walk is a bet on how far h moves: a walk at
+// 1.03 h0 serves converged smoothing lengths, at up to 1.25 h0 those that still
+// move, and where they move farther, or hold more candidates than fit, the targets
+// walk by themselves and a group walk before that is lost.  Losing it cost up to
+// twice the call: 1 M random particles with h 1.7 times too large 25 -> 52 ms, with
+// h 4% short 3.3 -> 4.5 ms.  So a sample of the targets takes its first Newton step
+// beforehand, in the launch that looks for the cells' largest h, a workgroup a
+// target with its lanes on the cells (12 us of a converged call; 2,048 samples of a
+// wavefront each 20).
+constexpr int kSamples = 512;
+inline int stage_samples(int64_t n) { return n < kSamples ? (int)n : kSamples; }
+// sampled targets that may miss the reach: one in 64 leaves a wavefront of the
+// walks by targets without any
+constexpr int kMissed = 64;
+// the largest reach of a group walk of the call, and the one to try first
+__host__ __device__ inline double stage_wide(const Params& P)
+{
+    return P.kappa < kFusedKappaMax ? P.kappa : kFusedKappaMax;
+}
+__host__ __device__ inline double stage_short(const Params& P)
+{
+    return P.kappa <= kFusedKappaMax ? fmin(kFusedReach, P.kappa) : kFusedKappaMax;
+}
+// The call's reach.  With a clamp inside the largest reach no h can leave that:
+// it is taken where more than one sampled h in 512 leaves the short one (by walks
+// of their own that many would cost as much again); its lists hold 1.8 times
+// the candidates (1 M random particles: 1.41 ms at the short reach, 2.41 at 1.25).
+__device__ __forceinline__ double stage_reach(const Params& P, const Domain* dom, int ns)
+{
+    const int grown = (int)dom->stage_grown, crowded = (int)dom->stage_crowded;
+    if (crowded * kMissed > ns) return 0.0;
+    if (P.kappa <= kFusedKappaMax) return grown * 512 > ns ? stage_wide(P) : stage_short(P);
+    return grown * kMissed > ns ? 0.0 : stage_wide(P);
+}
+
+// one sampled target, by the whole workgroup: bit 0 if its first Newton step leaves
+// the short reach, bit 1 if its candidates there would not fit (estimated from those
+// within 2 h)
+__device__ __forceinline__ uint32_t sample_target(const Params& P, const Domain& D,
+                                                  const CellRange* __restrict__ cells,
+                                                  const Pos4* __restrict__ p4, int cap, int64_t a)
+{
+    const int lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
+    const Pos4 pa = p4[a];
+    const double R = 2.0 * pa.h, R2 = R * R;
+    const double tsc = kPiHalfSq / (pa.h * pa.h);
+    const AxisWalk wx = axis_walk(P, D, 0, pa.x, R);
+    const AxisWalk wy = axis_walk(P, D, 1, pa.y, R);
+    const AxisWalk wz = axis_walk(P, D, 2, pa.z, R);
+    const int nx = wx.hi - wx.lo + 1, ny = wy.hi - wy.lo + 1, nz = wz.hi - wz.lo + 1;
+    const float ryz1 = 1.0f / (float)(ny * nz), rz1 = 1.0f / (float)nz;
+    const int ncells = nx > 0 && ny > 0 && nz > 0 ? nx * ny * nz : 0;
+    double sS = 0.0, sV = 0.0;
+    int cnt = 0;
+    auto add = [&](const Pos4& q) {
+        double dx, dy, dz;
+        const double r2 = disp(P, pa.x, pa.y, pa.z, q.x, q.y, q.z, dx, dy, dz);
+        if (r2 < R2) {
+            double S, vdS;
+            kern_terms(P, r2 * tsc, S, vdS);
+            sS += S;
+            sV += vdS;
+            ++cnt;
+        }
+    };
+    // What it takes is the latency of its loads, one after the other: a lane's
+    // cells are loaded together, then the first particles of all of them, then the
+    // rest in fours (the records have spare entries past the last slot); a wavefront
+    // shares what its fullest cells hold beyond 32.
+    constexpr int kU = 4, kFirst = 2, kOwn = 32;
+    for (int q0 = 0; q0 < ncells; q0 += kBlock * kU) {
+        CellRange cr[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int q = q0 + kBlock * u + (int)threadIdx.x;
+            cr[u] = CellRange{0, 0, 0.0};
+            if (q >= ncells) continue;
+            int ix, iy, iz;
+            box_cell(q, nx, ny, nz, ryz1, rz1, ix, iy, iz);
+            const double gx = axis_gap(wx, wx.lo + ix), gy = axis_gap(wy, wy.lo + iy);
+            const double gz = axis_gap(wz, wz.lo + iz);
+            if (gx * gx + gy * gy + gz * gz < R2)
+                cr[u] = cells[(spread10(axis_cell(wx, wx.lo + ix, D.ncell_axis)) << 2) |
+                              (spread10(axis_cell(wy, wy.lo + iy, D.ncell_axis)) << 1) |
+                              spread10(axis_cell(wz, wz.lo + iz, D.ncell_axis))];
+        }
+        Pos4 first[kU][kFirst];
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+#pragma unroll
+            for (int v = 0; v < kFirst; ++v) first[u][v] = p4[cr[u].s + v];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+#pragma unroll
+            for (int v = 0; v < kFirst; ++v)
+                if (cr[u].s + v < cr[u].e) add(first[u][v]);
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int32_t own = min(cr[u].e, cr[u].s + kOwn);
+            for (int32_t b = cr[u].s + kFirst; b < own; b += 4) {
+                Pos4 q[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) q[v] = p4[b + v];
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (b + v < own) add(q[v]);
+            }
+            uint64_t full = __ballot(cr[u].e - cr[u].s > kOwn);
+            while (full != 0u) {
+                const int l = __ffsll((unsigned long long)full) - 1;
+                full &= full - 1u;
+                const int32_t e = __builtin_amdgcn_readlane(cr[u].e, l);
+                for (int32_t b = __builtin_amdgcn_readlane(cr[u].s, l) + kOwn + lane; b < e; b += 64)
+                    add(p4[b]);
+            }
+        }
+    }
+    sS = group_sum<64>(sS);
+    sV = group_sum<64>(sV);
+    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
+    __shared__ double part[kBlock / 64][2];
+    __shared__ int count[kBlock / 64];
+    if (lane == 0) {
+        part[wv][0] = sS;
+        part[wv][1] = sV;
+        count[wv] = cnt;
+    }
+    __syncthreads();
+    sS = sV = 0.0;
+    cnt = 0;
+    for (int w = 0; w < kBlock / 64; ++w) {
+        sS += part[w][0];
+        sV += part[w][1];
+        cnt += count[w];
+    }
+    const double lam = stage_short(P);
+    return (newton_step(P, pa.h, pa.h, sS, sV) > lam * pa.h ? 1u : 0u) |
+           ((double)cnt * (lam * lam * lam) > (double)cap ? 2u : 0u);
+}
+
 // largest h per cell (for the symmetric search) and overall
 // (h is read from the slot-ordered array: consecutive cells read consecutive
-// runs of it); one atomic per workgroup of a bounded grid
+// runs of it); one atomic per workgroup of a bounded grid of `blocks`; each
+// workgroup past it takes one of sph_update_h's samples
 constexpr int kHmaxGrid = 512;
-__global__ __launch_bounds__(kBlock) void k_cells_max(Domain* __restrict__ dom,
+template <bool kSample>
+__global__ __launch_bounds__(kBlock) void k_cells_max(Params P, Domain* __restrict__ dom,
                                                       CellRange* __restrict__ cells,
-                                                      const double* __restrict__ h, int64_t cap)
+                                                      const double* __restrict__ h, int64_t cap,
+                                                      const Pos4* __restrict__ p4, int blocks)
 {
+    if (kSample && (int)blockIdx.x >= blocks) {
+        const int i = (int)blockIdx.x - blocks, ns = (int)gridDim.x - blocks;
+        const uint32_t bits =
+            sample_target(P, *dom, cells, p4, P.cand_cap, (2 * i + 1) * P.n / (2 * ns));
+        if (threadIdx.x < 2 && (bits >> threadIdx.x & 1u) != 0u) {
+            uint32_t* to = threadIdx.x == 0 ? &dom->stage_grown : &dom->stage_crowded;
+            // (past the decision the count does not matter)
+            if ((int)__hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) * kMissed <=
+                ns)
+                atomicAdd(to, 1u);
+        }
+        return;
+    }
     const int64_t ncell = min(int64_t(1) << (3 * dom->level), cap);
     double all = 0.0;
     for (int64_t c = blockIdx.x * (int64_t)kBlock + threadIdx.x; c < ncell;
-         c += (int64_t)gridDim.x * kBlock) {
+         c += (int64_t)blocks * kBlock) {
         double hm = 0.0;
         const CellRange cr = cells[c];
         for (int32_t b = cr.s; b < cr.e; ++b) hm = fmax(hm, h[b]);
@@ -327,15 +486,13 @@ __device__ __forceinline__ double reach_neighbor(const Params& P, int level, uin
 }
 
 // The stage entry points walk by groups too, at the h of the call: packed
-// positions and walk records for the reach 2 kap h (k2s its FP32 bound), with the
-// blocks' table and the call's words cleared
+// positions, with the blocks' table and the call's words cleared
 __global__ __launch_bounds__(kBlock) void k_stage_begin(Params P, Domain* __restrict__ dom,
                                                         const double* __restrict__ x,
                                                         const double* __restrict__ y,
                                                         const double* __restrict__ z,
                                                         const double* __restrict__ h,
                                                         Pos4* __restrict__ p4,
-                                                        Pos4f* __restrict__ pf, float k2s,
                                                         uint64_t* __restrict__ reach,
                                                         int64_t nreach)
 {
@@ -343,21 +500,27 @@ __global__ __launch_bounds__(kBlock) void k_stage_begin(Params P, Domain* __rest
     if (i == 0) {
         dom->hmax_new_bits = ord_bits(0.0);
         dom->refit = 0u;
+        dom->stage_grown = dom->stage_crowded = 0u;
     }
     if (i >= P.n) return;
-    const Pos4 q{x[i], y[i], z[i], h[i]};
-    p4[i] = q;
-    pf[i] = walk_record(dom, q, k2s);
+    p4[i] = Pos4{x[i], y[i], z[i], h[i]};
     if (i < nreach) reach[i] = 0ull;
 }
 
-// the blocks' largest h from the cells', at the level for a reach of 2 kap h
-__global__ __launch_bounds__(kBlock) void k_stage_reach(Domain* __restrict__ dom,
+// The call's reach (the lists' own, or chosen by the ns samples), the walk records
+// for it, and the blocks' largest h from the cells' at the level for it
+__global__ __launch_bounds__(kBlock) void k_stage_reach(Params P, Domain* __restrict__ dom,
                                                         const CellRange* __restrict__ cells,
-                                                        int64_t cap, double kap,
+                                                        int64_t cap, int ns,
+                                                        const Pos4* __restrict__ p4,
+                                                        Pos4f* __restrict__ pf,
                                                         uint64_t* __restrict__ reach)
 {
     const int64_t c = blockIdx.x * (int64_t)kBlock + threadIdx.x;
+    const double kap = ns > 0 ? stage_reach(P, dom, ns) : 1.0;
+    if (c == 0) dom->stage_reach = kap;
+    if (!(kap > 0.0)) return;
+    if (c < P.n) pf[c] = walk_record(dom, p4[c], up_f32(2.0 * kap));
     const int level = dom->level;
     const int rl = reach_level(*dom, 2.0 * kap * ord_value(dom->hmax_new_bits));
     if (c == 0) dom->reach_level = rl;
@@ -833,6 +996,8 @@ __global__ __launch_bounds__(64 * kSplit) SPH_WAVES_EXACT(kSplit > 1 ? 3 : SPH_W
     const int64_t nb = (P.n + kWalkT - 1) / kWalkT;
     const int64_t lb = xcd_block(nb);
     if (lb < 0) return;
+    if (stage) kap = dom->stage_reach;
+    if (!(kap > 0.0)) return;
     const int wv = kSplit > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : 0;
     WalkLds<kSplit>& S = lds[wv];
     const int lane = (int)threadIdx.x & 63, j = lane & 15, s = lane >> 4;
@@ -1467,6 +1632,10 @@ __global__ __launch_bounds__(kBlock) SPH_WAVES_EXACT(kG == 1 ? 4 : 3) void k_upd
 {
     constexpr int kTargets = kBlock / kG;
     const int64_t lb = xcd_block((P.n + kTargets - 1) / kTargets);
+    if (mode == kNewtonStage) {
+        lam = dom->stage_reach;
+        if (!(lam > 0.0)) return;
+    }
     if (lb >= 0) update_h_list<kPer, kTab, kG>(P, dom, nk, cand, p4, h, lam, flag, mode, lb);
 }
 // After the refits: the grown targets redo Newton over their full candidates,
@@ -1656,30 +1825,33 @@ int candidate_capacity(int ng_max)
     return cap > 8192 ? 8192 : cap;
 }
 
-// The group walk of a stage call: the candidates within 2 kap max(h_a, h_b) at the
-// present h, in Q's capacity.
+// The group walk of a stage call at the present h, in Q's capacity: the candidates
+// within 2 max(h_a, h_b), or (ns samples) within the reach that the samples choose.
 static hipError_t stage_candidates(const Params& Q, const Layout& L, const Ws& W,
-                                   const sph_particles* p, double kap, hipStream_t s)
+                                   const sph_particles* p, int ns, hipStream_t s)
 {
     const int64_t nb = (Q.n + kBlock - 1) / kBlock;
     const int64_t nreach = L.lcap > 2 ? int64_t(1) << (3 * (L.lcap - 2)) : 1;
     const int64_t cb = (L.ncells_cap + kBlock - 1) / kBlock;
-    k_stage_begin<<<nb, kBlock, 0, s>>>(Q, W.dom, p->x, p->y, p->z, p->h, W.p4, W.pf,
-                                        reach_f32(kap), W.reach, nreach);
-    k_cells_max<<<cb < kHmaxGrid ? cb : kHmaxGrid, kBlock, 0, s>>>(W.dom, W.cells, p->h,
-                                                                 L.ncells_cap);
-    k_stage_reach<<<cb, kBlock, 0, s>>>(W.dom, W.cells, L.ncells_cap, kap, W.reach);
-    launch_candidates(0, Q, W, kap, s, true);
+    const int mb = (int)(cb < kHmaxGrid ? cb : kHmaxGrid);
+    k_stage_begin<<<nb, kBlock, 0, s>>>(Q, W.dom, p->x, p->y, p->z, p->h, W.p4, W.reach, nreach);
+    if (ns > 0)
+        k_cells_max<true><<<mb + ns, kBlock, 0, s>>>(Q, W.dom, W.cells, p->h, L.ncells_cap, W.p4,
+                                                     mb);
+    else
+        k_cells_max<false><<<mb, kBlock, 0, s>>>(Q, W.dom, W.cells, p->h, L.ncells_cap, W.p4, mb);
+    k_stage_reach<<<nb, kBlock, 0, s>>>(Q, W.dom, W.cells, L.ncells_cap, ns, W.p4, W.pf, W.reach);
+    launch_candidates(0, Q, W, 1.0, s, true);
     return hipGetLastError();
 }
 
-// Newton over one walk's candidates, and by cell walks for the targets it flags:
-// those whose h left the candidates' reach, or with more candidates than fit.  The
-// reach is the fused step's short one (h near converged: few grow past 1.03 h0),
-// or 1.25 for the wider clamps of a set-up.  A walk per iteration and target took
-// 440 us at 262,144 particles and two iterations, and 295 us at 4,096 (64
-// wavefronts); this takes 260 and 50 us.  Where the order of the sums shows
-// (in_order) every target keeps the cell walks.
+// Newton over one walk's candidates, at the reach that stage_reach chooses, and by
+// cell walks for the targets it flags: those whose h left that reach, or with more
+// candidates than fit.  The call with a walk per iteration and target -> now, two
+// iterations: lattices of 4,096 317 -> 51 us (64 wavefronts), 262,144 523 -> 300,
+// 1 M random 3.49 -> 1.48 ms; all h short by 4%: 293 -> 63, 442 -> 427 us, 3.31 ->
+// 2.20 ms.  Where the order of the sums shows (in_order) every target keeps the
+// cell walks.
 hipError_t launch_update_h(const Params& P, const Layout& L, const Ws& W, sph_particles* p,
                            hipStream_t s, bool pack)
 {
@@ -1695,8 +1867,7 @@ hipError_t launch_update_h(const Params& P, const Layout& L, const Ws& W, sph_pa
     }
     Params Q = P;
     Q.cand_cap = L.cand_cap;
-    const double lam = P.kappa <= kFusedKappaMax ? fmin(kFusedReach, P.kappa) : kFusedKappaMax;
-    hipError_t e = stage_candidates(Q, L, W, p, lam, s);
+    hipError_t e = stage_candidates(Q, L, W, p, stage_samples(P.n), s);
     if (e != hipSuccess) return e;
     with_periodic(Q, [&](auto per) {
         with_table(Q, [&](auto tab) {
@@ -1705,7 +1876,7 @@ hipError_t launch_update_h(const Params& P, const Layout& L, const Ws& W, sph_pa
             with_lanes<4>(Q, [&](auto lanes) {
                 constexpr int kG = decltype(lanes)::value;
                 k_update_h_list<kPer, kTab, kG><<<grid_lanes(Q, kG), kBlock, 0, s>>>(
-                    Q, W.dom, W.nk, W.cand, W.p4, p->h, lam, W.flag, kNewtonStage);
+                    Q, W.dom, W.nk, W.cand, W.p4, p->h, 0.0, W.flag, kNewtonStage);
             });
         });
     });
@@ -1726,8 +1897,8 @@ hipError_t launch_find_neighbors(const Params& P, const Layout& L, const Ws& W,
         if (e != hipSuccess) return e;
         k_hmax_begin<<<1, 1, 0, s>>>(W.dom);
         const int64_t cb = (L.ncells_cap + kBlock - 1) / kBlock;
-        k_cells_max<<<cb < kHmaxGrid ? cb : kHmaxGrid, kBlock, 0, s>>>(W.dom, W.cells, p->h,
-                                                                     L.ncells_cap);
+        const int mb = (int)(cb < kHmaxGrid ? cb : kHmaxGrid);
+        k_cells_max<false><<<mb, kBlock, 0, s>>>(P, W.dom, W.cells, p->h, L.ncells_cap, W.p4, mb);
         k_check_range<<<1, 1, 0, s>>>(P, W.dom);
         k_find_neighbors<<<grid_xcd(nb), kBlock, 0, s>>>(P, W.dom, W.cells, W.p4, W.nc, W.ns,
                                                          W.list, nullptr, 0);
@@ -1735,7 +1906,7 @@ hipError_t launch_find_neighbors(const Params& P, const Layout& L, const Ws& W,
     }
     Params Q = P;
     Q.cand_cap = L.cand_cap;
-    hipError_t e = stage_candidates(Q, L, W, p, 1.0, s);
+    hipError_t e = stage_candidates(Q, L, W, p, 0, s);
     if (e != hipSuccess) return e;
     k_check_range<<<1, 1, 0, s>>>(P, W.dom);
     with_periodic(Q, [&](auto per) {
