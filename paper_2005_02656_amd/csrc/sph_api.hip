@@ -61,9 +61,10 @@ Layout make_layout(int64_t n, int ng_max)
     L.tabSf = take(sizeof(float2) * SPH_KERNEL_TABLE_MAX);
     L.tabDf = take(sizeof(float2) * SPH_KERNEL_TABLE_MAX);
     L.flag = take(sizeof(uint8_t) * n);
-    // the walk's reach bounds (the blocks' largest h, at least two levels above
-    // the cells, take the front; the size stands for callers that hold to
-    // sph_workspace_bytes and sph_step_static's limit)
+    // the walk's reach bounds: the blocks' largest h, at least two levels above the
+    // cells, take the first nreach words (the area stays as large as it was: what
+    // sph_workspace_bytes gives, and what sph_step_static refuses, stand)
+    L.nreach = lcap > 2 ? int64_t(1) << (3 * (lcap - 2)) : 1;
     size_t levels = 0;
     for (int l = 0; l < lcap; ++l) levels += size_t(1) << (3 * l);
     L.reach = take(sizeof(uint64_t) * (levels + (size_t)L.ncells_cap));

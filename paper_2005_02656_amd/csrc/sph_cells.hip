@@ -1,11 +1,10 @@
 // sph_cells.hip -- sph_build_cells: keep particles in the depth-first (Morton)
 // order of the octree (section 4.3).
 //
-//   1. bounding box of the open axes and largest h (each workgroup's extrema,
-//      combined by the last one to finish; min/max are exact and order-free, so
-//      the result is deterministic), and from them the domain record: key
-//      domain, 2^21 scale per axis, cell level;
-//   2. 63-bit keys (21 bits per axis, x highest in each bit triplet) + iota;
+//   1. bounding box of the open axes and largest h (each workgroup's extrema;
+//      min/max are exact and order-free, so the result is deterministic);
+//   2. from them the domain record (key domain, 2^21 scale per axis, cell level)
+//      and 63-bit keys (21 bits per axis, x highest in each bit triplet) + iota;
 //   3. stable LSD radix sort of (key, slot), 8 bits a pass.  Per pass:
 //      LDS tile histogram -> exclusive scan of the digit-major counts ->
 //      stable LDS-local ranking (wave ballots) -> tile reordered in LDS and
@@ -50,19 +49,26 @@ __device__ __forceinline__ double wave_max(double v)
     return v;
 }
 
-// the domain record, from the extrema of the open axes and the largest h
+// the key domain along an axis, from the extrema of the positions
+__device__ __forceinline__ void key_axis(const Params& P, int k, const double (&r)[7], double& lo,
+                                         double& hi, double& scale)
+{
+    lo = P.periodic[k] ? P.box_lo[k] : r[k];
+    hi = P.periodic[k] ? P.box_hi[k] : r[3 + k];
+    const double D = hi - lo;
+    scale = D > 0.0 ? 2097152.0 / D : 0.0;
+}
+
+// The domain record, from the extrema of the open axes and the largest h.  Nothing
+// in it but the error word outlives a cell build.
 __device__ void domain_record(const Params& P, Domain* d, const double (&r)[7], bool mv, bool uv)
 {
     double hm = r[6];
     if (!(hm > 0.0)) hm = 0.0;
     double D[3], ext = 0.0;
     for (int k = 0; k < 3; ++k) {
-        double lo = P.periodic[k] ? P.box_lo[k] : r[k];
-        double hi = P.periodic[k] ? P.box_hi[k] : r[3 + k];
-        d->lo[k] = lo;
-        d->hi[k] = hi;
-        D[k] = hi - lo;
-        d->scale[k] = (D[k] > 0.0) ? 2097152.0 / D[k] : 0.0;
+        key_axis(P, k, r, d->lo[k], d->hi[k], d->scale[k]);
+        D[k] = d->hi[k] - d->lo[k];
         ext = fmax(ext, D[k]);
     }
     // the walk's unit: ext is 1/2 .. 1 of it (1 where ext is 0 or no finite number)
@@ -90,24 +96,50 @@ __device__ void domain_record(const Params& P, Domain* d, const double (&r)[7], 
     d->mass_varies = mv ? 1u : 0u;
     d->u_varies = uv ? 1u : 0u;
     d->reach_level = reach_level(*d, 2.0 * P.kappa * hm);
+    d->arrived = 0u;
     d->built_n = P.n;
+}
+
+// Extrema over the first `waves` (at most kWaves) wavefronts of a workgroup into r,
+// mv and uv of thread 0
+__device__ __forceinline__ void block_extrema(double (&r)[7], bool& mv, bool& uv, int waves)
+{
+    __shared__ double s[kWaves][7];
+    __shared__ uint32_t flags[kWaves];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (w < waves) {
+        for (int k = 0; k < 3; ++k) r[k] = wave_min(r[k]);
+        for (int k = 3; k < 7; ++k) r[k] = wave_max(r[k]);
+        const uint32_t f = (__ballot(mv) ? 1u : 0u) | (__ballot(uv) ? 2u : 0u);
+        if (lane == 0) {
+            for (int k = 0; k < 7; ++k) s[w][k] = r[k];
+            flags[w] = f;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    uint32_t all = 0u;
+    for (int ww = 0; ww < waves; ++ww) {
+        for (int k = 0; k < 3; ++k) r[k] = fmin(r[k], s[ww][k]);
+        for (int k = 3; k < 7; ++k) r[k] = fmax(r[k], s[ww][k]);
+        all |= flags[ww];
+    }
+    mv = (all & 1u) != 0u;
+    uv = (all & 2u) != 0u;
 }
 
 // Bounding box of the open axes, largest h, and whether the masses and the
 // internal energies are all slot 0's (the passes then take the mass from there,
-// or the shorter momentum records).  Each workgroup leaves its extrema in `part`
-// and the last one to finish combines them into the domain record: one launch
-// instead of three, and one atomic per workgroup instead of seven on one line.
-// Bound by those atomics on one word up to a few million particles, hence the
-// small grid: 262,144 particles 63 + 9 us (the launches around it) -> 15 us, 1 M
-// 66 + 9 -> 22 us (512 workgroups 18 and 25).
+// or the shorter momentum records).  Each workgroup leaves its extrema in `part`;
+// the next launch combines them.  With atomics on one line instead 262,144
+// particles took 63 us and 1 M 66, and a launch for the record 9 more.
 __global__ __launch_bounds__(kBlock) void k_bbox(Params P, const double* __restrict__ x,
                                                  const double* __restrict__ y,
                                                  const double* __restrict__ z,
                                                  const double* __restrict__ h,
                                                  const double* __restrict__ m,
-                                                 const double* __restrict__ u, Domain* d,
-                                                 double* part)
+                                                 const double* __restrict__ u,
+                                                 double* __restrict__ part)
 {
     double r[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, -INFINITY};
     const double* pos[3] = {x, y, z};
@@ -127,59 +159,32 @@ __global__ __launch_bounds__(kBlock) void k_bbox(Params P, const double* __restr
         mv |= m[i] != m0;
         uv |= u[i] != u0;
     }
-    __shared__ double s[kWaves][7];
-    __shared__ uint32_t flags[kWaves];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    auto combine = [&]() {   // over the workgroup, into r and the flags of thread 0
-        for (int k = 0; k < 3; ++k) r[k] = wave_min(r[k]);
-        for (int k = 3; k < 7; ++k) r[k] = wave_max(r[k]);
-        const uint32_t f = (__ballot(mv) ? 1u : 0u) | (__ballot(uv) ? 2u : 0u);
-        if (lane == 0) {
-            for (int k = 0; k < 7; ++k) s[w][k] = r[k];
-            flags[w] = f;
-        }
-        __syncthreads();
-        uint32_t all = 0u;
-        for (int ww = 0; ww < kWaves; ++ww) {
-            for (int k = 0; k < 3; ++k) r[k] = fmin(r[k], s[ww][k]);
-            for (int k = 3; k < 7; ++k) r[k] = fmax(r[k], s[ww][k]);
-            all |= flags[ww];
-        }
-        mv = (all & 1u) != 0u;
-        uv = (all & 2u) != 0u;
-        __syncthreads();
-    };
-    combine();
-    if (threadIdx.x == 0) {
-        for (int k = 0; k < 7; ++k) put_partial(&part[blockIdx.x * 10 + k], r[k]);
-        put_partial(&part[blockIdx.x * 10 + 7], mv ? 1.0 : 0.0);
-        put_partial(&part[blockIdx.x * 10 + 8], uv ? 1.0 : 0.0);
-    }
-    if (!last_block(&d->arrived, gridDim.x)) return;
-    for (int b = threadIdx.x; b < (int)gridDim.x; b += kBlock) {
-        double v[9];
-#pragma unroll
-        for (int k = 0; k < 9; ++k) v[k] = get_partial(&part[b * 10 + k]);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) r[k] = fmin(r[k], v[k]);
-#pragma unroll
-        for (int k = 3; k < 7; ++k) r[k] = fmax(r[k], v[k]);
-        mv |= v[7] != 0.0;
-        uv |= v[8] != 0.0;
-    }
-    combine();
-    if (threadIdx.x == 0) domain_record(P, d, r, mv, uv);
+    block_extrema(r, mv, uv, kWaves);
+    if (threadIdx.x != 0) return;
+    double* out = part + blockIdx.x * 10;
+    for (int k = 0; k < 7; ++k) out[k] = r[k];
+    out[7] = mv ? 1.0 : 0.0;
+    out[8] = uv ? 1.0 : 0.0;
 }
 
 // keys and the digit counts of the sort's first pass, tile by tile; the cell
 // table and the blocks' largest h start from nothing here too (three launches
 // before).  1,024 threads a tile: with 256 the 64 tiles of 262,144 particles took
-// 22 us, now 10.
+// 22 us, now 10.  Every workgroup combines the extrema for itself, the first one
+// leaves the domain record: no workgroup waits for another, and no counter has to
+// hold a known value when a call begins.  The grid is bounded, as that takes some
+// microseconds each time, and the registers are held to two workgroups per CU (15.6
+// M particles, 3,815 tiles: 221 us without either, 177 with the first, 116 with
+// both).  With the record by the last workgroup of the launch before, the
+// two launches took 12.4 us at 1,000 particles, 24.6 at 262,144, 227 at 15.6 M; now
+// 11.2, 19.4 and 223.
 constexpr int kKeyThreads = 1024;
-__global__ __launch_bounds__(kKeyThreads) void k_keys(const double* __restrict__ x,
+constexpr int64_t kKeyGrid = 1024;
+static_assert(kRedGrid <= kBlock, "a thread of the first wavefronts per set of extrema");
+__global__ __launch_bounds__(kKeyThreads) SPH_WAVES_EXACT(8) void k_keys(Params P, const double* __restrict__ x,
                                                  const double* __restrict__ y,
-                                                 const double* __restrict__ z, int64_t n,
-                                                 const Domain* __restrict__ d,
+                                                 const double* __restrict__ z, Domain* d,
+                                                 const double* __restrict__ part, int nparts,
                                                  uint64_t* __restrict__ keys,
                                                  uint32_t* __restrict__ idx, int shift,
                                                  uint32_t* __restrict__ hist, int64_t nb,
@@ -187,25 +192,46 @@ __global__ __launch_bounds__(kKeyThreads) void k_keys(const double* __restrict__
                                                  uint64_t* __restrict__ reach, int64_t nreach)
 {
     __shared__ uint32_t hh[256];
-    if (threadIdx.x < 256) hh[threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t base = blockIdx.x * (int64_t)kSortTile;
+    __shared__ double lo[3], scale[3];
+    const int64_t n = P.n;
+    double r[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    bool mv = false, uv = false;
+    if ((int)threadIdx.x < nparts) {
+        const double* in = part + threadIdx.x * 10;
 #pragma unroll
-    for (int i = 0; i < kSortTile / kKeyThreads; ++i) {
-        const int64_t g = base + i * kKeyThreads + threadIdx.x;
-        if (g >= n) continue;
-        const uint32_t qx = quantize(x[g], d->lo[0], d->scale[0]);
-        const uint32_t qy = quantize(y[g], d->lo[1], d->scale[1]);
-        const uint32_t qz = quantize(z[g], d->lo[2], d->scale[2]);
-        const uint64_t key = morton3(qx, qy, qz);
-        keys[g] = key;
-        idx[g] = (uint32_t)g;
-        if (shift < 64) atomicAdd(&hh[(uint32_t)(key >> shift) & 255u], 1u);
-        if (g < ncells) cells[g] = CellRange{0, 0, 0.0};
-        if (g < nreach) reach[g] = 0ull;
+        for (int k = 0; k < 7; ++k) r[k] = in[k];
+        mv = in[7] != 0.0;
+        uv = in[8] != 0.0;
     }
+    block_extrema(r, mv, uv, (nparts + 63) / 64);
+    if (threadIdx.x == 0)
+        for (int k = 0; k < 3; ++k) {
+            double hi;
+            key_axis(P, k, r, lo[k], hi, scale[k]);
+        }
     __syncthreads();
-    if (threadIdx.x < 256) hist[(int64_t)threadIdx.x * nb + blockIdx.x] = hh[threadIdx.x];
+    if (blockIdx.x == 0 && threadIdx.x == 0) domain_record(P, d, r, mv, uv);
+    for (int64_t tile = blockIdx.x; tile < nb; tile += gridDim.x) {
+        if (threadIdx.x < 256) hh[threadIdx.x] = 0;
+        __syncthreads();
+        const int64_t base = tile * kSortTile;
+#pragma unroll
+        for (int i = 0; i < kSortTile / kKeyThreads; ++i) {
+            const int64_t g = base + i * kKeyThreads + threadIdx.x;
+            if (g >= n) continue;
+            const uint32_t qx = quantize(x[g], lo[0], scale[0]);
+            const uint32_t qy = quantize(y[g], lo[1], scale[1]);
+            const uint32_t qz = quantize(z[g], lo[2], scale[2]);
+            const uint64_t key = morton3(qx, qy, qz);
+            keys[g] = key;
+            idx[g] = (uint32_t)g;
+            if (shift < 64) atomicAdd(&hh[(uint32_t)(key >> shift) & 255u], 1u);
+            if (g < ncells) cells[g] = CellRange{0, 0, 0.0};
+            if (g < nreach) reach[g] = 0ull;
+        }
+        __syncthreads();
+        if (threadIdx.x < 256) hist[(int64_t)threadIdx.x * nb + tile] = hh[threadIdx.x];
+    }
 }
 
 // ------------------------------------------------------------------ radix sort
@@ -526,7 +552,7 @@ hipError_t launch_build_cells(const Params& P, const Layout& L, const Ws& W,
         k_fill_tables<<<(P.tab_n + kBlock - 1) / kBlock, kBlock, 0, s>>>(P, W.tabS, W.tabD,
                                                                           W.tabSf, W.tabDf);
     const int64_t rg = nb < kRedGrid ? nb : kRedGrid;
-    k_bbox<<<rg, kBlock, 0, s>>>(P, p->x, p->y, p->z, p->h, p->m, p->u, W.dom, W.sums);
+    k_bbox<<<rg, kBlock, 0, s>>>(P, p->x, p->y, p->z, p->h, p->m, p->u, W.sums);
 
     // Stable LSD radix sort by the key's prefix of lcap levels (3 lcap bits, 8
     // bits a pass): the depth-first order of the octree down to its finest
@@ -540,10 +566,11 @@ hipError_t launch_build_cells(const Params& P, const Layout& L, const Ws& W,
     uint64_t* kout = passes & 1 ? W.keys0 : W.keys1;
     uint32_t* iin = passes & 1 ? W.idx1 : W.idx0;
     uint32_t* iout = passes & 1 ? W.idx0 : W.idx1;
-    const int64_t nreach = L.lcap > 2 ? int64_t(1) << (3 * (L.lcap - 2)) : 1;
-    k_keys<<<L.nsort_blocks, kKeyThreads, 0, s>>>(p->x, p->y, p->z, n, W.dom, kin, iin, s0, W.hist,
+    const int64_t kg = L.nsort_blocks < kKeyGrid ? L.nsort_blocks : kKeyGrid;
+    k_keys<<<kg, kKeyThreads, 0, s>>>(P, p->x, p->y, p->z, W.dom, W.sums, (int)rg, kin,
+                                             iin, s0, W.hist,
                                              L.nsort_blocks, W.cells, L.ncells_cap, W.reach,
-                                             nreach);
+                                             L.nreach);
     for (int pass = 0; pass < passes; ++pass) {
         const int shift = s0 + 8 * pass;
         if (pass > 0)

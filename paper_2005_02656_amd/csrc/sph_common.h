@@ -72,7 +72,7 @@ struct Domain {
     uint32_t nonuniform;       // some m or c differs from slot 0's (full momentum records)
     uint32_t mass_varies;      // some m differs from slot 0's (set by the cell build)
     uint32_t u_varies;         // some u differs from slot 0's (set by the cell build)
-    uint32_t arrived;          // workgroups done (last_block); 0 between launches
+    uint32_t arrived;          // workgroups done (last_block); 0 from the cell build on
     int32_t reach_level;       // level of the blocks that bound each group walk's reach
     // stage calls: sampled targets whose h grows past, or whose candidates overrun,
     // the reach at hand, and the reach (0: every target walks the cells by itself)
@@ -162,12 +162,14 @@ __host__ __device__ inline int64_t lpos(int64_t a, int j, int cap)
     return ((a >> 6) * (int64_t)cap + j) * 64 + (a & 63);
 }
 
-// Candidate lists (fused step) are stored in chunks of 8 entries per slot: the
-// 8 entries j..j+7 (j a multiple of 8) of slot a are 32 contiguous bytes, and
-// the 64 slots of a wavefront tile keep their chunks side by side.  The walk
-// appends into registers and writes whole chunks (the writes are not lane-
-// synchronous, so one 4-byte write per entry left lines partly written); the
-// readers load one chunk per batch of 8.  cap is a multiple of 8.
+// Candidate lists are stored in chunks of 8 entries per slot: the 8 entries
+// j..j+7 (j a multiple of 8) of slot a are 32 contiguous bytes, and the 64 slots
+// of a wavefront tile keep their chunks side by side.  The walks stage a target's
+// candidates in LDS and write whole chunks (one 4-byte write per entry, at places
+// that differ from lane to lane, left lines partly written); wavefronts that share
+// a group, and the few refits by a wavefront each, write entry by entry.  Readers
+// take a chunk per lane (one lane per target), pairs (4 lanes) or single entries
+// (16).  cap is a multiple of 8.
 __host__ __device__ inline int64_t lpos8(int64_t a, int j, int cap)
 {
     return (((a >> 6) * (int64_t)(cap >> 3) + (j >> 3)) * 64 + (a & 63)) * 8 + (j & 7);
@@ -204,7 +206,7 @@ struct Layout {
     size_t tabS, tabD, tabSf, tabDf;
     size_t flag, reach;
     size_t total;
-    int64_t n, nsort_blocks, hist_len, scan_blocks, ncells_cap;
+    int64_t n, nsort_blocks, hist_len, scan_blocks, ncells_cap, nreach;
     int lcap, cand_cap;
 };
 Layout make_layout(int64_t n, int ng_max);
@@ -231,7 +233,7 @@ struct Ws {
     double2 *tabS, *tabD;      // kernel tables (kernel_table > 0), FP64 and FP32
     float2 *tabSf, *tabDf;
     uint8_t* flag;             // fused step: 2 h left the short reach, 1 a neighbour of one
-    uint64_t* reach;           // fused step: largest h per block of the reach level (its bits)
+    uint64_t* reach;           // largest h per block of the reach level (its bits)
 };
 Ws carve(void* ws, const Layout& L);
 
@@ -490,7 +492,9 @@ SPH_DEV double group_sum(double v)
 // so the line is drawn at 65,536 (for IAD, whose pair work is small, at 16,384:
 // 18 against 15 us at 30,011).  Above it 4 lanes (Newton, filter, momentum: 731
 // us at 1 M, 721 with 2, 804 with 1, 944 with 8; clustered 8 M: 8.8, 9.4, 10.8
-// and 10.0 ms) or 2 (IAD: 288 us at 1 M, 294 with 4, 312 with 1).
+// and 10.0 ms) or 2 (IAD; one, two and four lanes on lattices of 74,088 particles
+// 41, 32, 28 us, 262,144 77, 78, 84, 1 M 330, 296, 308; random 124,999 66, 56, 51,
+// 262,144 123, 112, 107).
 constexpr int64_t kLanesSmall = 65536;
 constexpr int64_t kLanesSmallIad = 16384;
 // calls f(std::integral_constant<int, kG>) with 16 lanes per target for up to
@@ -505,10 +509,13 @@ inline void with_lanes(const Params& P, F&& f, int64_t small = kLanesSmall)
 // density or of C now and then rounds to another FP32 value in the momentum
 // records.  Under the weakly compressible EOS, where P = p_ref + c0^2 (rho -
 // rho_ref) magnifies the density's last bits, several lanes per target moved the
-// rates of the 1 M-particle square patch by 7e-9, and single particles by 6e-6.
-// So the passes that feed or form mixed rates keep one lane per target there and
-// the candidates in the order of the cells; only the ideal gas up to `small`
-// particles, where such a rounding is rarer than one in 100 steps, takes 16.
+// rates of the 1 M-particle square patch by up to 9e-8 of the largest (single
+// particles by 6e-6 of their own).  The passes that feed or form mixed rates keep
+// one lane per target there, and above `small` particles, with the candidates in
+// the order of the cells: the bits of the sums in list order.  It is a choice of
+// bits, not of accuracy: against FP64 the accelerations of that patch are off by
+// 2.237e-6 rms in one order and in the other, those of 262,144 lattice particles
+// by 8.803e-7, of 30,011 random ones by 2.550e-7.
 inline bool in_order(const Params& P, int64_t small = kLanesSmall)
 {
     return P.precision == SPH_MIXED &&
