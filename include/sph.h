@@ -221,7 +221,8 @@ sph_status sph_step_marked(const sph_config* cfg, sph_particles* p, sph_globals*
 /* (host) A HIP graph of `steps` consecutive sph_step calls (section 4.1: the
  * whole time step, `steps` times) on these particles, globals and workspace,
  * replayed by one launch.  Small problems are bound by the launch cost of the
- * step's ~40 kernels; a graph hands the device the whole sequence at once.
+ * step's 18 kernels (28 from 262,144 particles on); a graph hands the device the
+ * whole sequence at once.
  * The step is captured on a stream of the library's own (the caller's stream
  * may be the legacy default stream, which cannot be captured) and nothing is
  * run at creation; every sph_step_graph_launch then enqueues the steps on
@@ -368,7 +369,8 @@ sph_status sph_neighbors_view(const sph_config* cfg, void* ws, const int32_t** n
 #define SPH_SHORT_REACH 1.03
 
 /* (host) Device pointers into ws after sph_step with h_ratio_max <= 1.25 (the
- * fused path): nk (int32[n]), each slot's candidate count, and the candidate
+ * fused path) and until the next call on ws (sph_update_h and sph_find_neighbors
+ * keep candidates of their own there): nk (int32[n]), each slot's candidate count, and the candidate
  * capacity per slot.  The candidates of a slot are every b != a within
  * 2*lambda*max(h0_a, h0_b) (lambda = min(SPH_SHORT_REACH, h_ratio_max), or h_ratio_max
  * when the full-reach pass ran), plus any pairs the FP32 prefilter's rounding

@@ -152,8 +152,11 @@ __global__ __launch_bounds__(kBlock) void k_uniform_check(int64_t n, const doubl
 }
 
 // The IAD sums are bound by the address path (one 32-byte record per pair); two
-// lanes per target: 1 M particles 308 -> 288 us, 8 M clustered 2.99 ms as before,
-// 262,144 (one particle per cell) 74 -> 80 us, 1,000 27 -> 7 us.
+// lanes per target, before (one) -> now: lattices of 1,000 27 -> 7 us, 74,088 40 ->
+// 32, 512,000 163 -> 161, 1 M 316 -> 296; random 124,999 65 -> 56, 262,144 129 ->
+// 112; an Evrard sphere of 262,144 121 -> 106; 8 M clustered 2.99 ms as before.  The
+// one loss found is the lattice of 262,144, one particle to a cell: 74 -> 78 (one
+// lane 77 there now).
 template <int kPer, bool kTab, int kG>
 __global__ __launch_bounds__(kBlock) SPH_WAVES_CAP(SPH_WAVES_IAD) void k_iad(Params P, Domain* __restrict__ dom,
                                                 const int32_t* __restrict__ nc,

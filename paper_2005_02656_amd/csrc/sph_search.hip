@@ -1,12 +1,12 @@
 // sph_search.hip -- smoothing-length Newton update and neighbour search.
 //
-// Cell walk of the stage entry points: one thread per target slot; consecutive
-// slots are Morton-consecutive, so the lanes of a wavefront sit in a few
-// neighbouring cells and walk mostly the same candidate cells (same-address
-// loads across lanes, served from L1/L2).  Cells are smaller than the kernel reach (edge >= h_max/2); each
-// target walks its own stencil and skips cells whose box is out of reach, with a
-// margin covering the rounding of the key quantisation.  Candidate positions and
-// h come from the packed 32-byte records.
+// Cells are smaller than the kernel reach (edge >= h_max/2).  The walks of groups
+// of 16 neighbouring targets test FP32 records of positions and reaches (below);
+// the walks of one target per thread, over the packed 32-byte records, take their
+// own stencil and skip cells whose box is out of reach, with a margin covering the
+// rounding of the key quantisation.  Consecutive slots are Morton-consecutive, so
+// the lanes of a wavefront sit in a few neighbouring cells and walk mostly the same
+// ones (same-address loads across lanes, served from L1/L2).
 //
 // Three compositions use these kernels:
 //  * the fused step: ONE walk, by groups of neighbouring targets, collects
@@ -14,7 +14,8 @@
 //    needs, since the Newton clamp keeps h <= kappa h0), the Newton iterations sum
 //    over the candidate list, and a filter pass writes the exact lists from the
 //    candidates with the final h;
-//  * the stage entry points: the same, a walk each for Newton and for the lists;
+//  * the stage entry points: the same, a walk each for Newton (its reach chosen
+//    by a sample) and for the lists;
 //  * one target per lane by cell walks, for targets that the candidates of a stage
 //    call do not serve and where the order of the sums has to stand.
 //    The neighbour sets are identical; only the visiting order differs.
@@ -642,8 +643,8 @@ __device__ __forceinline__ float walk_r2(const Domain& D, float xa, float ya, fl
 
 // ---------------------------------------------------------------- fused step
 // Candidates: every b != a with r^2 < (2 kap max(h0_a, h0_b))^2 (kap: the reach
-// factor of this pass), by the same per-target cell walk over 16-byte FP32
-// records.  The test runs in FP32 on offsets from the domain's low corner, with
+// factor of this pass), by walks of the cells over 16-byte FP32 records.  The test
+// runs in FP32 on offsets from the domain's low corner, with
 // the reach widened by a bound on their rounding (the cell build stores each
 // particle's widened squared reach in its record): each offset is within
 // 2^-24 ext of its FP64 value (ext: the largest extent of the key domain); the
@@ -1155,15 +1156,16 @@ again:
                     if (kPer & 1) x = fmaf(-wl[0], rintf(x * wi[0]), x);
                     if (kPer & 2) y = fmaf(-wl[1], rintf(y * wi[1]), y);
                     if (kPer & 4) z = fmaf(-wl[2], rintf(z * wi[2]), z);
+                    w2 = fmaf(z, z, fmaf(y, y, x * x));
+                    w = w2 - (w + e2);
                     // past the end, and at no position: an infinite distance,
                     // which no reach of any size accepts (an accepted place past
                     // the end would name whatever the queue holds there)
-                    w2 = fmaf(z, z, fmaf(y, y, x * x));
                     const bool there = ok && w2 < INFINITY;
                     x = there ? x : 0.0f;
                     y = there ? y : 0.0f;
                     z = there ? z : 0.0f;
-                    w = there ? w2 - (w + e2) : INFINITY;
+                    w = there ? w : INFINITY;
                     w2 = there ? w2 : INFINITY;
                 }
                 const int at = (p >> 5) * kWalkRow + (p & 31);
@@ -1831,10 +1833,10 @@ static hipError_t stage_candidates(const Params& Q, const Layout& L, const Ws& W
                                    const sph_particles* p, int ns, hipStream_t s)
 {
     const int64_t nb = (Q.n + kBlock - 1) / kBlock;
-    const int64_t nreach = L.lcap > 2 ? int64_t(1) << (3 * (L.lcap - 2)) : 1;
     const int64_t cb = (L.ncells_cap + kBlock - 1) / kBlock;
     const int mb = (int)(cb < kHmaxGrid ? cb : kHmaxGrid);
-    k_stage_begin<<<nb, kBlock, 0, s>>>(Q, W.dom, p->x, p->y, p->z, p->h, W.p4, W.reach, nreach);
+    k_stage_begin<<<nb, kBlock, 0, s>>>(Q, W.dom, p->x, p->y, p->z, p->h, W.p4, W.reach,
+                                        L.nreach);
     if (ns > 0)
         k_cells_max<true><<<mb + ns, kBlock, 0, s>>>(Q, W.dom, W.cells, p->h, L.ncells_cap, W.p4,
                                                      mb);
