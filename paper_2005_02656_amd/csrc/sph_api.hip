@@ -61,13 +61,15 @@ Layout make_layout(int64_t n, int ng_max)
     L.tabSf = take(sizeof(float2) * SPH_KERNEL_TABLE_MAX);
     L.tabDf = take(sizeof(float2) * SPH_KERNEL_TABLE_MAX);
     L.flag = take(sizeof(uint8_t) * n);
-    // the walk's reach bounds: the blocks' largest h, at least two levels above the
-    // cells, take the first nreach words (the area stays as large as it was: what
-    // sph_workspace_bytes gives, and what sph_step_static refuses, stand)
+    // the walk's reach bounds: the blocks' largest h and fullest cells, at least two
+    // levels above the cells, take the first 2 nreach words (the area stays as large
+    // as it was, which is more: what sph_workspace_bytes gives, and what
+    // sph_step_static refuses, stand)
     L.nreach = lcap > 2 ? int64_t(1) << (3 * (lcap - 2)) : 1;
     size_t levels = 0;
     for (int l = 0; l < lcap; ++l) levels += size_t(1) << (3 * l);
-    L.reach = take(sizeof(uint64_t) * (levels + (size_t)L.ncells_cap));
+    const size_t words = levels + (size_t)L.ncells_cap, used = 2 * (size_t)L.nreach;
+    L.reach = take(sizeof(uint64_t) * (words > used ? words : used));   // (256-byte units)
     L.total = o;
     return L;
 }
@@ -104,6 +106,7 @@ Ws carve(void* ws, const Layout& L)
     W.tabDf = (float2*)(b + L.tabDf);
     W.flag = (uint8_t*)(b + L.flag);
     W.reach = (uint64_t*)(b + L.reach);
+    W.fullest = W.reach + L.nreach;
     return W;
 }
 

@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kKeyThreads) SPH_WAVES_EXACT(8) void k_keys(Params 
             idx[g] = (uint32_t)g;
             if (shift < 64) atomicAdd(&hh[(uint32_t)(key >> shift) & 255u], 1u);
             if (g < ncells) cells[g] = CellRange{0, 0, 0.0};
-            if (g < nreach) reach[g] = 0ull;
+            if (g < nreach) reach[g] = reach[nreach + g] = 0ull;   // and the fullest cells
         }
         __syncthreads();
         if (threadIdx.x < 256) hist[(int64_t)threadIdx.x * nb + tile] = hh[threadIdx.x];

@@ -234,6 +234,7 @@ struct Ws {
     float2 *tabSf, *tabDf;
     uint8_t* flag;             // fused step: 2 h left the short reach, 1 a neighbour of one
     uint64_t* reach;           // largest h per block of the reach level (its bits)
+    uint64_t* fullest;         // fused step: particles of each block's fullest cell, if many
 };
 Ws carve(void* ws, const Layout& L);
 

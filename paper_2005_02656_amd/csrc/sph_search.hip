@@ -28,6 +28,10 @@ namespace sph {
 namespace {
 
 constexpr double kCullMargin = 1e-9;  // relative to the cell edge
+// particles of a cell that a refit by a wavefront takes with all lanes together: a
+// lane by itself needs some 150 cycles a particle, all together some 600 for each
+// of up to 64 cells
+constexpr uint32_t kRefitFat = 128;
 
 // particle records of one cell loaded together by the cell walk (a batch may
 // read up to kCellBatch - 1 records past the cell's end: the record arrays keep
@@ -464,10 +468,10 @@ __device__ __forceinline__ uint32_t compact10(uint32_t v)
     return v;
 }
 
-// largest h of the i-th of block c and its 26 neighbours at the reach level,
-// i = 0 .. 26 (wrapped on periodic axes, 0 beyond the edge of open ones)
-__device__ __forceinline__ double reach_neighbor(const Params& P, int level, uint32_t c, int i,
-                                                 const uint64_t* __restrict__ reach)
+// entry of a blocks' table for the i-th of block c and its 26 neighbours at the
+// reach level, i = 0 .. 26 (wrapped on periodic axes, 0 beyond the edge of open ones)
+__device__ __forceinline__ uint64_t block_neighbor(const Params& P, int level, uint32_t c, int i,
+                                                   const uint64_t* __restrict__ table)
 {
     const int nb = 1 << level;
     int q[3] = {(int)compact10(c >> 2) + i / 9 - 1, (int)compact10(c >> 1) + i / 3 % 3 - 1,
@@ -480,10 +484,16 @@ __device__ __forceinline__ double reach_neighbor(const Params& P, int level, uin
             else in = false;
         }
     }
-    if (!in) return 0.0;
+    if (!in) return 0u;
     const uint32_t cc = (spread10((uint32_t)q[0]) << 2) | (spread10((uint32_t)q[1]) << 1) |
                         spread10((uint32_t)q[2]);
-    return __builtin_bit_cast(double, reach[cc]);
+    return table[cc];
+}
+// its largest h
+__device__ __forceinline__ double reach_neighbor(const Params& P, int level, uint32_t c, int i,
+                                                 const uint64_t* __restrict__ reach)
+{
+    return __builtin_bit_cast(double, block_neighbor(P, level, c, i, reach));
 }
 
 // The stage entry points walk by groups too, at the h of the call: packed
@@ -536,8 +546,9 @@ __global__ __launch_bounds__(kBlock) void k_stage_reach(Params P, Domain* __rest
     }
 }
 
-// The fused step's largest h per cell and per block of the reach level (whose
-// table the cell build cleared), and the step's flags.  h is still the cell
+// The fused step's largest h per cell and per block of the reach level, the
+// particles of each block's fullest cell (tables that the cell build cleared), and
+// the step's flags.  h is still the cell
 // build's, so its largest value is known and no word is shared by all
 // workgroups: 262,144 particles 46 -> 5 us, and eleven launches fewer than with a
 // level-by-level reduction, its bounds and the flags' resets.  h >= 0, so its bits
@@ -545,23 +556,32 @@ __global__ __launch_bounds__(kBlock) void k_stage_reach(Params P, Domain* __rest
 __global__ __launch_bounds__(kBlock) void k_cells_reach(Params P, Domain* __restrict__ dom,
                                                         CellRange* __restrict__ cells,
                                                         const double* __restrict__ h, int64_t cap,
-                                                        uint64_t* __restrict__ reach)
+                                                        uint64_t* __restrict__ reach,
+                                                        uint64_t* __restrict__ fullest)
 {
     const int64_t c = blockIdx.x * (int64_t)kBlock + threadIdx.x;
     const int level = dom->level;
     const int64_t ncell = min(int64_t(1) << (3 * level), cap);
     double hm = 0.0;
+    int cnt = 0;
     if (c < ncell) {
         const CellRange cr = cells[c];
         for (int32_t b = cr.s; b < cr.e; ++b) hm = fmax(hm, h[b]);
         cells[c].hmax = hm;
+        cnt = cr.e - cr.s;
     }
     for (int o = 32; o > 0; o >>= 1) hm = fmax(hm, __shfl_xor(hm, o, 64));
+    const uint64_t most = (uint64_t)wave_max_i(cnt);
     if ((threadIdx.x & 63) == 0 && c < ncell && hm > 0.0) {
         const uint64_t bits = __builtin_bit_cast(uint64_t, hm);
-        uint64_t* at = &reach[c >> (3 * (level - dom->reach_level))];
+        const int64_t block = c >> (3 * (level - dom->reach_level));
+        uint64_t* at = &reach[block];
         if (bits > __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
             atomicMax((unsigned long long*)at, (unsigned long long)bits);
+        at = &fullest[block];
+        if (most > kRefitFat &&
+            most > __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax((unsigned long long*)at, (unsigned long long)most);
     }
     if (c == 0) {
         dom->refit = 0u;
@@ -671,6 +691,9 @@ __device__ __forceinline__ float walk_r2(const Domain& D, float xa, float ya, fl
 // is for 512 slots with few flagged ones (refit_few), a lane each for the others
 // (a whole step with all particles grown, by lanes over an unbounded grid and now:
 // lattices of 262,144 1.62, 1.49 ms, 1 M 6.04, 5.77; 262,144 random 3.20, 2.61).
+// Where a cell near by holds more than kRefitFat particles, as in a clump whose
+// cells are sized for its surroundings, a lane's walk takes milliseconds and the
+// wavefront's lanes share such cells.
 // Both walk a target's cells, and write its candidates, in the same order.
 //
 // kMode 1: the targets whose h left the short reach (flag 2), marking every
@@ -720,6 +743,31 @@ __device__ __forceinline__ void refit_target(
                 }
             }
         }
+        // full cells (a clump in cells sized for its surroundings): one after the
+        // other, all lanes on its particles, in the same order
+        if (__ballot(e - b0 > (int32_t)kRefitFat) != 0u) {
+            uint64_t cells_left = __ballot(e > b0);
+            while (cells_left != 0u) {
+                const int l = __ffsll((unsigned long long)cells_left) - 1;
+                cells_left &= cells_left - 1u;
+                const int32_t end = __builtin_amdgcn_readlane(e, l);
+                for (int32_t s = __builtin_amdgcn_readlane(b0, l); s < end; s += 64) {
+                    const int32_t b = s + lane;
+                    const Pos4f r = pf[b < end ? b : s];
+                    const float r2 = walk_r2<kPer>(D, fa.x, fa.y, fa.z, r.x, r.y, r.z);
+                    const bool near = b < end && b != (int32_t)a &&
+                                      __float_as_uint(r2) < max(far2, __float_as_uint(r.r2 * sc));
+                    const uint64_t m = __ballot(near);
+                    const int at = k + __popcll(m & ((uint64_t(1) << lane) - 1u));
+                    if (near) {
+                        if (kMode == 1 && flag[b] == 0) flag[b] = 1;
+                        if (at < cap) cand[lpos8(a, at & ~7, cap) + (at & 7)] = b;
+                    }
+                    k += __popcll(m);
+                }
+            }
+            continue;
+        }
         // its accepted particles: counted first, for their places, then written
         auto each = [&](auto&& take) {
             for (int32_t b = b0; b < e; b += 4) {
@@ -759,7 +807,10 @@ __device__ __forceinline__ void refit_target(
 }
 
 // flagged targets among 512 up to which each has a wavefront: about 16,000 of them
-// in all, or half
+// in all, or half; near full cells 96, where the lanes' walks of 512 targets take as
+// long (8 wavefronts, 150 cycles a particle) as so many wavefronts' (600 cycles a
+// cell and 9 a particle, some 100 cells of 20,000 particles)
+constexpr int kRefitFewFat = 96;
 __device__ inline int refit_few(const Params& P)
 {
     const int64_t t = (int64_t(1) << 23) / P.n;
@@ -778,7 +829,8 @@ __global__ __launch_bounds__(kBlock) SPH_WAVES_EXACT(5) void k_candidates_full(
     Params P, Domain* __restrict__ dom, const CellRange* __restrict__ cells,
     const Pos4* __restrict__ p4, const Pos4f* __restrict__ pf, int32_t* __restrict__ nk,
     int32_t* __restrict__ cand, double kap, float sc, uint8_t* __restrict__ flag,
-    const uint64_t* __restrict__ keys, const uint64_t* __restrict__ reach)
+    const uint64_t* __restrict__ keys, const uint64_t* __restrict__ reach,
+    const uint64_t* __restrict__ fullest)
 {
     if (dom->refit == 0u) return;
     // a bounded grid: a launch that finds nothing to do costs its workgroups'
@@ -812,7 +864,10 @@ __global__ __launch_bounds__(kBlock) SPH_WAVES_EXACT(5) void k_candidates_full(
         if (any == 0u) continue;
         int found = mine;
         for (int o = 32; o > 0; o >>= 1) found += __shfl_xor(found, o, 64);
-        if (found <= refit_few(P)) {
+        const int one = __ffsll((unsigned long long)any) - 1;   // a lane with a flagged target
+        const uint32_t near = (uint32_t)(keys[s0 + 8 * one] >> (3 * (kKeyBits - dom->reach_level)));
+        const bool fat = lane < 27 && block_neighbor(P, dom->reach_level, near, lane, fullest) > 0u;
+        if (found <= (__ballot(fat) != 0u ? max(refit_few(P), kRefitFewFat) : refit_few(P))) {
             // one target after the other, the wavefront's lanes on its cells
             uint64_t todo = __ballot(((uint32_t)(f >> (8 * (g & 7))) & 0xffu) == kWant &&
                                      (share == 8 || (lane & 7) == g >> 3));
@@ -1316,10 +1371,17 @@ again:
             const int start = fill + inc - cnt;
             int w0 = 0;   // the windows completed by this round's cells
             for (;;) {
-                const int i1 = min(cnt, w0 + kWalkWin - start);
-                for (int i = max(0, w0 - start); i < i1; ++i)
-                    S.queue[qbase + start + i - w0] = (uint32_t)(cr.s + i);
                 const int have = fill + total - w0;
+                // (in fours: one cell may fill windows by itself, and its lane alone
+                // queues them)
+                int i = max(0, w0 - start);
+                const int i1 = min(cnt, w0 + kWalkWin - start);
+                uint32_t* to = &S.queue[qbase + start - w0];
+                for (; i + 4 <= i1; i += 4) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) to[i + v] = (uint32_t)(cr.s + i + v);
+                }
+                for (; i < i1; ++i) to[i] = (uint32_t)(cr.s + i);
                 if (have < kWalkWin && (have == 0 || q0 + 64 < qe)) {
                     fill = have;
                     break;
@@ -1399,10 +1461,12 @@ static void launch_candidates(int mode, const Params& P, const Ws& W, double kap
         constexpr int kPer = decltype(per)::value;
         if (mode == 1)
             k_candidates_full<kPer, 1><<<few, kBlock, 0, s>>>(
-                P, W.dom, W.cells, W.p4, W.pf, W.nk, W.cand, kap, sc, W.flag, W.keys0, W.reach);
+                P, W.dom, W.cells, W.p4, W.pf, W.nk, W.cand, kap, sc, W.flag, W.keys0, W.reach,
+                W.fullest);
         else if (mode == 2)
             k_candidates_full<kPer, 2><<<few, kBlock, 0, s>>>(
-                P, W.dom, W.cells, W.p4, W.pf, W.nk, W.cand, kap, sc, W.flag, W.keys0, W.reach);
+                P, W.dom, W.cells, W.p4, W.pf, W.nk, W.cand, kap, sc, W.flag, W.keys0, W.reach,
+                W.fullest);
         else if (in_order(P))
             k_candidates<kPer, true, 1><<<grid_xcd((P.n + kWalkT - 1) / kWalkT), 64, 0, s>>>(
                 P, W.dom, W.cells, W.p4, W.pf, W.nk, W.cand, kap, W.keys0, W.reach, stage);
@@ -1649,9 +1713,20 @@ __global__ __launch_bounds__(kBlock) SPH_WAVES_EXACT(kG == 1 ? 4 : 3) void k_upd
     const int32_t* __restrict__ cand, Pos4* p4, double* h, double lam,
     uint8_t* __restrict__ flag)
 {
+    constexpr int kTargets = kBlock / kG;
+    const int64_t nb = (P.n + kTargets - 1) / kTargets;
+    if constexpr (kG == 1) {
+        // (a workgroup per 256 targets: in a loop 27 registers spill, 680 -> 950 us
+        // with all of a 1 M patch grown)
+        const int64_t lb = xcd_block(nb);
+        const int64_t a = lb * kBlock + threadIdx.x;
+        if (lb < 0) return;
+        if (dom->refit != 0u && lam > kFusedReach)
+            update_h_list<kPer, kTab, 1>(P, dom, nk, cand, p4, h, lam, flag, kNewtonRefit, lb);
+        if (a < P.n) p4[a].h = h[a];
+        return;
+    }
     if (dom->refit != 0u && lam > kFusedReach) {
-        constexpr int kTargets = kBlock / kG;
-        const int64_t nb = (P.n + kTargets - 1) / kTargets;
         for (int64_t bid = blockIdx.x; bid < grid_xcd(nb); bid += gridDim.x) {
             const int64_t lb = xcd_block(nb, bid);
             if (lb < 0) continue;
@@ -1931,7 +2006,7 @@ hipError_t launch_fused_step(const Params& P, const Layout& L, const Ws& W, sph_
                              hipStream_t s, const Marks& mk)
 {
     const int64_t cb = (L.ncells_cap + kBlock - 1) / kBlock;
-    k_cells_reach<<<cb, kBlock, 0, s>>>(P, W.dom, W.cells, p->h, L.ncells_cap, W.reach);
+    k_cells_reach<<<cb, kBlock, 0, s>>>(P, W.dom, W.cells, p->h, L.ncells_cap, W.reach, W.fullest);
     mk.at(0, s);
     // short reach first; the full-reach pair runs only if an h left it (the
     // kernels read the device flag and return at once when it is clear)
@@ -1959,7 +2034,7 @@ hipError_t launch_fused_step(const Params& P, const Layout& L, const Ws& W, sph_
             launch_candidates(2, P, W, P.kappa, s);
         }
         const int64_t nb = (P.n + kBlock - 1) / kBlock;
-        const int grid = (int)(nb < kRefitNewtonGrid ? nb : kRefitNewtonGrid);
+        const int64_t grid = in_order(P) ? grid_xcd(nb) : nb < kRefitNewtonGrid ? nb : kRefitNewtonGrid;
         with_periodic(P, [&](auto per) {
             with_table(P, [&](auto tab) {
                 constexpr int kPer = decltype(per)::value;
