@@ -267,9 +267,11 @@ __global__ void k_hmax_begin(Domain* d) { d->hmax_new_bits = ord_bits(0.0); }
 // wavefront each 20).
 constexpr int kSamples = 512;
 inline int stage_samples(int64_t n) { return n < kSamples ? (int)n : kSamples; }
-// sampled targets that may miss the reach: one in 64 leaves a wavefront of the
-// walks by targets without any
-constexpr int kMissed = 64;
+// One sampled target in kMissed without room for its candidates, or in kLost that
+// grows past the largest reach, and all walk by themselves.  (Targets that grow lie
+// together, at the edge of a clump that is too wide, and the rest gains more than
+// their walks cost; where h is too large a group walk is dear whoever misses it.)
+constexpr int kMissed = 64, kLost = 8;
 // the largest reach of a group walk of the call, and the one to try first
 __host__ __device__ inline double stage_wide(const Params& P)
 {
@@ -288,12 +290,13 @@ __device__ __forceinline__ double stage_reach(const Params& P, const Domain* dom
     const int grown = (int)dom->stage_grown, crowded = (int)dom->stage_crowded;
     if (crowded * kMissed > ns) return 0.0;
     if (P.kappa <= kFusedKappaMax) return grown * 512 > ns ? stage_wide(P) : stage_short(P);
-    return grown * kMissed > ns ? 0.0 : stage_wide(P);
+    return grown * kLost > ns ? 0.0 : stage_wide(P);
 }
 
 // one sampled target, by the whole workgroup: bit 0 if its first Newton step leaves
-// the short reach, bit 1 if its candidates there would not fit (estimated from those
-// within 2 h)
+// the short reach, bit 1 if it shrinks by more than a quarter (h some 1.5 times too
+// large: the walks by targets follow it, a list does not) or its candidates would not
+// fit (estimated from those within 2 h)
 __device__ __forceinline__ uint32_t sample_target(const Params& P, const Domain& D,
                                                   const CellRange* __restrict__ cells,
                                                   const Pos4* __restrict__ p4, int cap, int64_t a)
@@ -392,9 +395,9 @@ __device__ __forceinline__ uint32_t sample_target(const Params& P, const Domain&
         sV += part[w][1];
         cnt += count[w];
     }
-    const double lam = stage_short(P);
-    return (newton_step(P, pa.h, pa.h, sS, sV) > lam * pa.h ? 1u : 0u) |
-           ((double)cnt * (lam * lam * lam) > (double)cap ? 2u : 0u);
+    const double lam = stage_short(P), h1 = newton_step(P, pa.h, pa.h, sS, sV);
+    return (h1 > lam * pa.h ? 1u : 0u) |
+           (h1 < 0.78 * pa.h || (double)cnt * (lam * lam * lam) > (double)cap ? 2u : 0u);
 }
 
 // largest h per cell (for the symmetric search) and overall
@@ -415,8 +418,7 @@ __global__ __launch_bounds__(kBlock) void k_cells_max(Params P, Domain* __restri
         if (threadIdx.x < 2 && (bits >> threadIdx.x & 1u) != 0u) {
             uint32_t* to = threadIdx.x == 0 ? &dom->stage_grown : &dom->stage_crowded;
             // (past the decision the count does not matter)
-            if ((int)__hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) * kMissed <=
-                ns)
+            if ((int)__hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) * kLost <= ns)
                 atomicAdd(to, 1u);
         }
         return;
