@@ -379,8 +379,7 @@ def main():
 
     if not args.no_graph:
         # the same step replayed from a one-step HIP graph (sph_step_graph):
-        # what the eager steps lose to launching their kernels (18, or 28 from 262,144
-        # particles on) one by one
+        # what the eager steps lose to launching their 16 to 28 kernels one by one
         sg = sph.StepGraph(cfg, parts, g, ws, steps=1)
         sg.launch(stream)
         torch.cuda.synchronize()

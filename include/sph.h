@@ -221,7 +221,7 @@ sph_status sph_step_marked(const sph_config* cfg, sph_particles* p, sph_globals*
 /* (host) A HIP graph of `steps` consecutive sph_step calls (section 4.1: the
  * whole time step, `steps` times) on these particles, globals and workspace,
  * replayed by one launch.  Small problems are bound by the launch cost of the
- * step's 18 kernels (28 from 262,144 particles on); a graph hands the device the
+ * step's 16 to 28 kernels; a graph hands the device the
  * whole sequence at once.
  * The step is captured on a stream of the library's own (the caller's stream
  * may be the legacy default stream, which cannot be captured) and nothing is
