@@ -21,8 +21,12 @@ constexpr int kSortItems = 16;                      // keys per thread per tile
 constexpr int kSortTile = kBlock * kSortItems;      // 4096
 constexpr int kWaves = kBlock / 64;
 constexpr int kWaveItems = kSortTile / kWaves;      // 1024 consecutive keys per wave
-constexpr int kRedGrid = 256;                       // bbox reduction blocks
-static_assert(kRedGrid <= kSumBlocks, "the partial extrema share the sums' area");
+// workgroups of the bounding box: 256, and from 1 M particles on one per 4,096 up to
+// 1,024 (256 leave too few loads in flight there: a whole cell build of 4.1, 15.6 and
+// 64 M particles took 0.774, 2.865 and 11.12 ms with 256, 0.730, 2.70 and 10.38 now.
+// 1,024 at 262,144 cost this launch and the next 23.4 us against 20.0)
+constexpr int64_t kRedGrid = 256, kRedGridMax = 1024;
+static_assert(kRedGridMax <= kSumBlocks, "the partial extrema share the sums' area");
 #ifndef SPH_CELL_FACTOR
 #define SPH_CELL_FACTOR 0.5
 #endif
@@ -176,11 +180,9 @@ __global__ __launch_bounds__(kBlock) void k_bbox(Params P, const double* __restr
 // microseconds each time, and the registers are held to two workgroups per CU (15.6
 // M particles, 3,815 tiles: 221 us without either, 177 with the first, 116 with
 // both).  With the record by the last workgroup of the launch before, the
-// two launches took 12.4 us at 1,000 particles, 24.6 at 262,144, 227 at 15.6 M; now
-// 11.2, 19.4 and 223.
+// two launches took 12.4 us at 1,000 particles and 24.6 at 262,144; now 11.2 and 20.0.
 constexpr int kKeyThreads = 1024;
 constexpr int64_t kKeyGrid = 1024;
-static_assert(kRedGrid <= kBlock, "a thread of the first wavefronts per set of extrema");
 __global__ __launch_bounds__(kKeyThreads) SPH_WAVES_EXACT(8) void k_keys(Params P, const double* __restrict__ x,
                                                  const double* __restrict__ y,
                                                  const double* __restrict__ z, Domain* d,
@@ -196,14 +198,18 @@ __global__ __launch_bounds__(kKeyThreads) SPH_WAVES_EXACT(8) void k_keys(Params 
     const int64_t n = P.n;
     double r[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, -INFINITY};
     bool mv = false, uv = false;
-    if ((int)threadIdx.x < nparts) {
-        const double* in = part + threadIdx.x * 10;
+    if (threadIdx.x < kBlock) {
+        for (int i = threadIdx.x; i < nparts; i += kBlock) {
+            const double* in = part + i * 10;
 #pragma unroll
-        for (int k = 0; k < 7; ++k) r[k] = in[k];
-        mv = in[7] != 0.0;
-        uv = in[8] != 0.0;
+            for (int k = 0; k < 3; ++k) r[k] = fmin(r[k], in[k]);
+#pragma unroll
+            for (int k = 3; k < 7; ++k) r[k] = fmax(r[k], in[k]);
+            mv |= in[7] != 0.0;
+            uv |= in[8] != 0.0;
+        }
     }
-    block_extrema(r, mv, uv, (nparts + 63) / 64);
+    block_extrema(r, mv, uv, min((nparts + 63) / 64, kWaves));
     if (threadIdx.x == 0)
         for (int k = 0; k < 3; ++k) {
             double hi;
@@ -551,7 +557,8 @@ hipError_t launch_build_cells(const Params& P, const Layout& L, const Ws& W,
     if (P.tab_n > 0)
         k_fill_tables<<<(P.tab_n + kBlock - 1) / kBlock, kBlock, 0, s>>>(P, W.tabS, W.tabD,
                                                                           W.tabSf, W.tabDf);
-    const int64_t rg = nb < kRedGrid ? nb : kRedGrid;
+    const int64_t wanted = nb / 16 < kRedGrid ? kRedGrid : nb / 16 < kRedGridMax ? nb / 16 : kRedGridMax;
+    const int64_t rg = nb < wanted ? nb : wanted;
     k_bbox<<<rg, kBlock, 0, s>>>(P, p->x, p->y, p->z, p->h, p->m, p->u, W.sums);
 
     // Stable LSD radix sort by the key's prefix of lcap levels (3 lcap bits, 8
